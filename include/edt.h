@@ -338,7 +338,7 @@ edt_status edt_batch_destroy(edt_batch* batch);
  * int32[nz][ny][nx], written in place by the three passes.  The extent must
  * satisfy nx^2 + ny^2 + nz^2 < 2^31 (every squared distance fits in int32),
  * else EDT_ERR_ARG.  The caller's workspace (8-byte aligned,
- * edt_dense_workspace_bytes) holds the per-column parabola envelopes.
+ * edt_dense_workspace_bytes) holds row records or column envelopes.
  * The incremental form is the dense context below. */
 #define EDT_DENSE_INF 0x7fffffff
 int64_t edt_dense_workspace_bytes(int32_t nx, int32_t ny, int32_t nz);
@@ -349,7 +349,7 @@ edt_status edt_dense_global(int32_t nx, int32_t ny, int32_t nz, int32_t d_max,
 /* Allocation-free form of edt_dense_global, for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc).  Same arguments and result, without the
- * workspace: the column envelopes live in a static device buffer of the
+ * workspace: its content lives in a static device buffer of the
  * library, EDT_DENSE_STATIC_BYTES (64 MiB) on each GPU it runs on, held
  * until the process ends.  Grids with edt_dense_workspace_bytes(nx, ny, nz)
  * above that (more than 8,388,608 voxels, e.g. beyond 256 x 256 x 128)

@@ -8,18 +8,25 @@
 // EDT_DENSE_INF.  Values are int32: the extent must satisfy
 // nx^2 + ny^2 + nz^2 < 2^31, so every squared distance fits.
 //
-// Three passes over the caller's int32 output array, in place:
-//   x   one wave per row, 64 voxels per step: a ballot of the occupancy
-//       bytes gives, per lane, the nearest obstacle at or left of it (and in
-//       a second sweep at or right of it), carried across steps;
+// Three passes.  Extents up to HULL_NX x HULL_N x HULL_N:
+//   x   the occupancy becomes one record per 32 voxels of a row (the bits and
+//       the distances of the first and last voxel, k_dense_rows), from which
+//       any distance along x follows;
+//   y,z the lower envelope of the parabolas q -> f(v) + (q - v)^2 of every
+//       column (Felzenszwalb and Huttenlocher's separable transform, the one
+//       the paper cites in section I), built and read in LDS by bands of 32
+//       rows (edt_hull.h): memory is touched once per voxel and pass.
+// Longer sides, in place over the caller's array:
+//   x   one wave per row: a ballot of the occupancy bytes gives, per lane,
+//       the nearest obstacle at or left of it (and in a second sweep at or
+//       right of it), carried across steps;
 //   y,z one lane per column (64 consecutive x per wave, coalesced rows): the
-//       lower envelope of the parabolas q -> f(v) + (q - v)^2 of the column's
-//       finite values (Felzenszwalb and Huttenlocher's separable transform,
-//       the one the paper cites in section I), built left to right with
-//       parabola intersections compared exactly as int64 cross products,
-//       then read off left to right.  The envelope of every column lives in
-//       the workspace (one int2 (v, f) per voxel), entry k of column c at
-//       k * ncols + c.
+//       same envelope built left to right with parabola intersections
+//       compared exactly as int64 cross products, then read off left to
+//       right.  The envelope of every column lives in the workspace (one int2
+//       (v, f) per voxel), entry k of column c at k * ncols + c.
+// On the 1024 x 1024 x 128 tunnel extent the first form takes 0.85 ms, the
+// second 2.99 ms (its stacks are touched one cache line per lane and push).
 //
 // The dense context (edt_dense_ctx_*) keeps the occupancy and both
 // intermediates (g1 after x, g2 after y) beside the field, so a change list
@@ -34,9 +41,11 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "edt.h"
 #include "edt_dev.h"
+#include "edt_hull.h"
 
 // Scratch of the allocation-free entry point (edt_dense_global_noalloc): the
 // column envelopes of grids up to EDT_DENSE_STATIC_BYTES / 8 voxels.  Each
@@ -499,6 +508,284 @@ __global__ void __launch_bounds__(64) k_dense_col_y2(int nx, int ny, int nz,
     }
 }
 
+// ---------------------------------------------------------------------------
+// extents up to HULL_NX x HULL_N x HULL_N: row records and banded hulls
+// ---------------------------------------------------------------------------
+// Bits of 32 voxels, nonzero bytes of v, bit i = byte i.
+__device__ inline uint32_t bytes8_bits(uint32_t a, uint32_t b) {
+    // bit 7 of every byte: the byte is nonzero; the dot products weigh them
+    // with 1, 2, 4, .. 128
+    const uint32_t ta = ((((a & 0x7f7f7f7fu) + 0x7f7f7f7fu) | a) >> 7) & 0x01010101u;
+    const uint32_t tb = ((((b & 0x7f7f7f7fu) + 0x7f7f7f7fu) | b) >> 7) & 0x01010101u;
+    return __builtin_amdgcn_udot4(ta, 0x08040201u,
+                                  __builtin_amdgcn_udot4(tb, 0x80402010u, 0u, false), false);
+}
+__device__ inline uint32_t bytes32_bits(const uint8_t* p) {
+    uint32_t v[8];
+    __builtin_memcpy(v, p, 32);                 // rows start at any byte
+    return bytes8_bits(v[0], v[1]) | (bytes8_bits(v[2], v[3]) << 8) |
+           (bytes8_bits(v[4], v[5]) << 16) | (bytes8_bits(v[6], v[7]) << 24);
+}
+
+// Occupancy word w (voxels 32 w .. 32 w + 31) of a row of nx voxels.
+__device__ inline uint32_t row_word(const uint8_t* row, int nx, int w) {
+    const int x0 = 32 * w;
+    if (x0 + 32 <= nx) return bytes32_bits(row + x0);
+    if (nx >= 32) return bytes32_bits(row + nx - 32) >> (x0 + 32 - nx);   // the row's last 32
+    uint32_t m = 0u;
+    for (int k = 0; k < nx; ++k) m |= (row[k] != 0 ? 1u : 0u) << k;
+    return m;
+}
+
+// Record of word w of a row: the occupancy word and the distances of its
+// first and last voxel (row_distance).  Called by the wave's lanes with
+// W >= ceil(nx / 32) consecutive lanes (W a power of two, w = lane % W) on
+// one row; word = 0 for words past the row.
+__device__ inline uint2 row_record(uint32_t word, int w, int W) {
+    constexpr int NONE = 1 << 20;
+    int last = word ? 32 * w + 31 - __clz(word) : -NONE;      // at or before this word's end
+    int first = word ? 32 * w + __ffs(word) - 1 : NONE;       // at or after its start
+    const int own_last = last, own_first = first;
+    for (int d = 1; d < W; d <<= 1) {
+        const int u = __shfl_up(last, d, W), v = __shfl_down(first, d, W);
+        if (w >= d) last = max(last, u);
+        if (w + d < W) first = min(first, v);
+    }
+    int before = __shfl_up(last, 1, W), after = __shfl_down(first, 1, W);
+    if (w == 0) before = -NONE;
+    if (w == W - 1) after = NONE;
+    const int x0 = 32 * w, x1 = x0 + 31;
+    const int d0 = min(min(own_first, after) - x0, x0 - before);
+    const int d1 = min(x1 - max(own_last, before), after - x1);
+    return make_uint2(word, (uint32_t)min(d0, 0xffff) | ((uint32_t)min(d1, 0xffff) << 16));
+}
+
+// Row records of the whole grid, rec[(z * nw + w) * ny + y] (y fastest, so a
+// group of 32 columns reads them in order).  A workgroup takes RB rows of one
+// z and turns the records round in LDS, so that they leave in runs of RB.
+// Bound by the read of the occupancy (134 MB in 34 us on 1024 x 1024 x 128;
+// writing int32 distances along x instead took 206 us, most of it the 537 MB).
+template <int W>
+__global__ void __launch_bounds__(256) k_dense_rows(int nx, int ny, int nz, int nw,
+                                                    const uint8_t* __restrict__ occ, uint2* rec) {
+    constexpr int RPW = 64 / W;                          // rows of a wave's step
+    constexpr int RB = 4 * RPW < 16 ? 16 : 4 * RPW;      // rows of a workgroup
+    __shared__ uint2 buf[RB * (W + 1)];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int w = lane & (W - 1);
+    const int nyb = (ny + RB - 1) / RB;
+    for (int64_t g = blockIdx.x; g < (int64_t)nyb * nz; g += gridDim.x) {
+        const int z = (int)(g / nyb), y0 = (int)(g % nyb) * RB;
+        for (int r0 = 0; r0 < RB; r0 += 4 * RPW) {
+            const int r = r0 + wave * RPW + lane / W, y = y0 + r;
+            uint32_t word = 0u;
+            if (w < nw && y < ny) word = row_word(occ + ((int64_t)z * ny + y) * nx, nx, w);
+            buf[r * (W + 1) + w] = row_record(word, w, W);
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < RB * nw; i += 256) {
+            const int r = i % RB, ww = i / RB;
+            if (y0 + r < ny) rec[((int64_t)z * nw + ww) * ny + y0 + r] = buf[r * (W + 1) + ww];
+        }
+        __syncthreads();
+    }
+}
+
+// Incremental form: the listed rows only (each row's flag is cleared); a word
+// whose record changed lists its y group (w, z).  A record is a function of
+// the 32 distances behind it, so it changes only where one of them does.
+template <int W>
+__global__ void __launch_bounds__(256) k_dense_rows_inc(int nx, int ny, int nw,
+                                                        const uint8_t* __restrict__ occ,
+                                                        uint2* rec, DenseMarks mk) {
+    constexpr int RPW = 64 / W;
+    if (blockIdx.x == 0 && threadIdx.x == 0) mk.cnt[DC_CANCEL] = 0;   // its last reader is done
+    const int lane = threadIdx.x & 63, w = lane & (W - 1);
+    const int64_t rows = mk.cnt[DC_NROW];
+    const int64_t step = (int64_t)gridDim.x * 4 * RPW;
+    for (int64_t i0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * RPW; i0 < rows; i0 += step) {
+        const int64_t ri = i0 + lane / W;
+        const bool live = ri < rows;
+        const int64_t r = live ? (int64_t)mk.rows[ri] : 0;
+        if (live && w == 0) mk.rowflag[r] = 0;
+        uint32_t word = 0u;
+        if (live && w < nw) word = row_word(occ + r * nx, nx, w);
+        const uint2 n = row_record(word, w, W);
+        if (live && w < nw) {
+            const int z = (int)(r / ny), y = (int)(r % ny);
+            uint2* p = rec + ((int64_t)z * nw + w) * ny + y;
+            const uint2 o = *p;
+            if (o.x != n.x || o.y != n.y) {
+                *p = n;
+                list_once(mk.gy, mk.ly, &mk.cnt[DC_NY], (int64_t)w + (int64_t)nw * z);
+            }
+        }
+    }
+}
+
+// Passes y (AXIS 1, from the row records to `out`) and z (AXIS 2, from `in`
+// to `out`, in place if they are the same array): one workgroup per group of
+// 32 consecutive x at one z (y), one lane per column and band of 32 rows; the
+// group's envelope lives in LDS (edt_hull.h), so the pass touches memory once
+// per voxel.  INC: only the listed groups (each group's flag is cleared);
+// pass y lists the z group (x / 32, y) of every y whose value changed.
+//
+// Bound by VALU issue: 77 (y) and 87 (z) instructions a row, 0.26 and 0.30 ms
+// of issue in 0.40 and 0.42 ms on 1024 x 1024 x 128 (1.38 and 1.38 ms with
+// one lane per column and the envelope in memory).  Registers: 64 for y, so
+// that two workgroups of 1024 lanes share a CU and one works while the other
+// waits at a merge; 96 for z, whose LDS (16.6 KB of 128 lanes at 128 rows)
+// leaves nine workgroups.
+template <int AXIS>
+using HullEntry = typename std::conditional<AXIS == 1, uint16_t, uint32_t>::type;
+
+template <int AXIS, bool INC>
+__global__ void __launch_bounds__(1024, AXIS == 1 ? 8 : 5) k_dense_hull(int nx, int ny, int nz, int nw,
+                                                     const uint2* __restrict__ rec,
+                                                     const int32_t* in, int32_t* out, int32_t cap,
+                                                     DenseMarks mk) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int n = AXIS == 1 ? ny : nz, other = AXIS == 1 ? nz : ny;
+    const int nb = hull_bands(n);
+    using T = HullEntry<AXIS>;
+    const HullLds<T> h = hull_lds<T>(lds, n);
+    const int t = threadIdx.x, col = t & (HC - 1), band = t / HC;
+    const int64_t stride = AXIS == 1 ? (int64_t)nx : (int64_t)nx * ny;
+    const int64_t groups = INC ? (int64_t)mk.cnt[AXIS == 1 ? DC_NY : DC_NZ] : (int64_t)nw * other;
+    for (int64_t gi = blockIdx.x; gi < groups; gi += gridDim.x) {
+        const int64_t gr = INC ? (int64_t)(AXIS == 1 ? mk.ly : mk.lz)[gi] : gi;
+        if (INC && t == 0) (AXIS == 1 ? mk.gy : mk.gz)[gr] = 0;
+        const int w = (int)(gr % nw), o = (int)(gr / nw);
+        const int x = w * HC + col;
+        const bool live = x < nx && band < nb;
+        const int i0 = band * HB;
+        const int64_t base = AXIS == 1 ? (int64_t)x + (int64_t)nx * ny * o
+                                       : (int64_t)x + (int64_t)nx * o;
+        if (t < HC) h.nem[t] = 0u;
+        // the band's rows into LDS, and the mask of those that can matter
+        T* own = h.st + band * HB * HC + col;
+        HullMask mask(band, n);
+        uint32_t acc = 0u;                       // bit r: row r - 1
+        if (AXIS == 1) {
+            // each lane of the half wave fetches one record; all read them
+            // from LDS row by row
+            uint2* recs = (uint2*)(lds + hull_lds_bytes<T>(n)) + i0;
+            if (band < nb) {
+                const int y = i0 + col;
+                recs[col] = y < n ? rec[((int64_t)o * nw + w) * ny + y]
+                                  : make_uint2(0u, 0xffffffffu);
+            }
+            __syncthreads();
+            if (band < nb) {
+#pragma unroll 1
+                for (int r0 = 0; r0 < HB; r0 += 8) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const int r = r0 + u;
+                        const uint2 q = recs[r];
+                        const uint32_t d = row_distance(q.x, q.y, col);
+                        mask.row(d >= 0xffffu ? HINF : hull_mul((int)d, (int)d) + r * r, 1u << u);
+                        own[r * HC] = (T)((d << 5) | (uint32_t)r);
+                    }
+                    acc |= mask.bits << r0;
+                    mask.bits = 0u;
+                }
+            }
+        } else {
+            const int32_t* src = in + base + stride * i0;
+            for (int r0 = 0; r0 < HB; r0 += 16) {
+                int32_t f[16];
+                if (live && i0 + r0 + 16 <= n) {
+#pragma unroll
+                    for (int u = 0; u < 16; ++u, src += stride) f[u] = *src;
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 16; ++u, src += stride) {
+                        f[u] = DINF;
+                        if (live && i0 + r0 + u < n) f[u] = *src;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    const int r = r0 + u;
+                    mask.row(f[u] == DINF ? HINF : f[u] + r * r, 1u << u);
+                    if (band < nb) own[r * HC] = (T)(((uint32_t)f[u] << 5) | (uint32_t)r);
+                }
+                acc |= mask.bits << r0;
+                mask.bits = 0u;
+            }
+        }
+        mask.row(HINF, 0x80000000u);
+        __syncthreads();
+        if (live) {
+            const int k = hull_scan(own, (acc >> 1) | mask.bits);
+            h.rng[band * HC + col] = (uint16_t)(k << 8);
+            if (k) atomicOr(&h.nem[col], 1u << band);
+        }
+        __syncthreads();
+        for (int s = 1; s < nb; s <<= 1) {
+            const int lb = 2 * band * s;                 // pair `band` of this level
+            if (lb + s < nb && x < nx) {
+                const uint32_t m = (1u << s) - 1u;
+                const uint32_t dead = hull_merge(h, col, h.nem[col], m << lb, m << (lb + s));
+                if (dead) atomicAnd(&h.nem[col], ~dead);
+            }
+            __syncthreads();
+        }
+        const uint32_t m = live ? h.nem[col] : 0u;
+        if ((m >> band) & 1u) hull_enter(h, col, band, m);
+        __syncthreads();
+        if ((m >> band) & 1u) hull_cover(h, col, band, nb, m);
+        __syncthreads();
+        if (band < nb) {
+            HullCursor<T> c;
+            if (m) {
+                const int b = h.start[band * HC + col];
+                c.init(h, col, m, b, hull_start(h, col, b, i0));
+            }
+            int32_t* dst = out + base + stride * i0;
+            const int rows = min(HB, n - i0);
+#pragma unroll 1
+            for (int r0 = 0; r0 < rows; r0 += HO) {
+                int32_t res[HO], old[HO];
+                if (INC && AXIS == 1) {
+                    const int32_t* was = dst;
+#pragma unroll
+                    for (int u = 0; u < HO; ++u, was += stride) {
+                        old[u] = 0;
+                        if (live && r0 + u < rows) old[u] = *was;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < HO; ++u) res[u] = cap;
+                if (m) c.take(h, col, i0 + r0, res);
+                if (live) {
+                    int32_t* d = dst;
+#pragma unroll
+                    for (int u = 0; u < HO; ++u, d += stride) {
+                        if (r0 + u >= rows) continue;
+                        if (AXIS == 2 && !INC) __builtin_nontemporal_store(res[u], d);
+                        else *d = res[u];
+                    }
+                }
+                dst += HO * stride;
+                if (INC && AXIS == 1) {
+#pragma unroll
+                    for (int u = 0; u < HO; ++u) {
+                        const bool ch = live && r0 + u < rows && old[u] != res[u];
+                        const unsigned long long b = __ballot(ch);
+                        const uint32_t half = (t & 32) ? (uint32_t)(b >> 32) : (uint32_t)b;
+                        if (half && col == 0)
+                            list_once(mk.gz, mk.lz, &mk.cnt[DC_NZ],
+                                      (int64_t)w + (int64_t)nw * (i0 + r0 + u));
+                    }
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // Incremental update of the dense context, step 1: range check and
 // voxel-keyed dedupe (the last entry of a voxel wins), as in the sparse
 // update.  ukeys / uvals: open-addressing table of capacity umask + 1.
@@ -578,15 +865,55 @@ bool dense_ok(int32_t nx, int32_t ny, int32_t nz) {
     return d2 < (int64_t)edt::DINF;
 }
 
+// Extents of the banded hulls: one mask bit a band, and values below 2^23.
+bool hull_ok(int nx, int ny, int nz) {
+    return nx <= edt::HULL_NX && ny <= edt::HULL_N && nz <= edt::HULL_N;
+}
+int row_words(int nx) { return (nx + 31) / 32; }
+
+// Calls f with the lanes a row takes (the power of two >= its words) as a
+// compile-time constant.
+template <class F>
+void with_row_lanes(int nw, F&& f) {
+    if (nw > 32) f(std::integral_constant<int, 64>());
+    else if (nw > 16) f(std::integral_constant<int, 32>());
+    else if (nw > 8) f(std::integral_constant<int, 16>());
+    else if (nw > 4) f(std::integral_constant<int, 8>());
+    else if (nw > 2) f(std::integral_constant<int, 4>());
+    else if (nw > 1) f(std::integral_constant<int, 2>());
+    else f(std::integral_constant<int, 1>());
+}
+// LDS of the row records of a group along y.
+int row_lds_bytes(int ny) { return edt::hull_bands(ny) * edt::HB * (int)sizeof(uint2); }
+dim3 hull_threads(int n) { return dim3((edt::hull_bands(n) * edt::HC + 63) & ~63); }
+
 // The three passes of the dense transform on `st`: x into g1, y from g1 into
-// g2, z from g2 into s (the same array for the in-place transform),
-// envelopes in env.
+// g2, z from g2 into s (g2 and s may be the same array), envelopes in env.
+// Within hull_ok, g1 holds row records (8 bytes per 32 voxels) and env is
+// not used.
 edt_status launch_dense3(int32_t nx, int32_t ny, int32_t nz, int32_t d_max, const uint8_t* d_occ,
                          int32_t* g1, int32_t* g2, int32_t* s, int2* env, hipStream_t st) {
     using namespace edt;
     const int32_t cap = d_max > 0 ? d_max * d_max : DINF;
-    const int nxc = (nx + 63) / 64;
     const DenseMarks none{};
+    if (hull_ok(nx, ny, nz)) {
+        const int nw = row_words(nx);
+        uint2* rec = (uint2*)g1;
+        with_row_lanes(nw, [&](auto lanes) {
+            constexpr int W = decltype(lanes)::value, RB = 256 / W < 16 ? 16 : 256 / W;
+            hipLaunchKernelGGL(k_dense_rows<W>,
+                               dim3(grid_of((int64_t)((ny + RB - 1) / RB) * nz, 65536)), dim3(256),
+                               0, st, nx, ny, nz, nw, d_occ, rec);
+        });
+        hipLaunchKernelGGL((k_dense_hull<1, false>), dim3(grid_of((int64_t)nw * nz, 65536)),
+                           hull_threads(ny), hull_lds_bytes<uint16_t>(ny) + row_lds_bytes(ny), st, nx, ny, nz, nw,
+                           (const uint2*)rec, (const int32_t*)nullptr, g2, (int32_t)DINF, none);
+        hipLaunchKernelGGL((k_dense_hull<2, false>), dim3(grid_of((int64_t)nw * ny, 65536)),
+                           hull_threads(nz), hull_lds_bytes<uint32_t>(nz), st, nx, ny, nz, nw,
+                           (const uint2*)nullptr, (const int32_t*)g2, s, cap, none);
+        return hipGetLastError() == hipSuccess ? EDT_OK : EDT_ERR_HIP;
+    }
+    const int nxc = (nx + 63) / 64;
     hipLaunchKernelGGL(k_dense_x<false>, dim3(grid_of((int64_t)ny * nz, 65536)), dim3(64), 0, st,
                        nx, ny, nz, d_occ, g1, none);
     // chunk lengths measured on a 1024x1024x128 extent: 16 for the long y
@@ -600,12 +927,13 @@ edt_status launch_dense3(int32_t nx, int32_t ny, int32_t nz, int32_t d_max, cons
     return EDT_OK;
 }
 
-// The three passes of the dense transform on `st`, in place on d_out,
-// envelopes in env.
+// The three passes of the dense transform on `st` into d_out, with the
+// caller's workspace (8 bytes per voxel): row records or envelopes.
 edt_status launch_dense(int32_t nx, int32_t ny, int32_t nz, int32_t d_max, const uint8_t* d_occ,
                         int32_t* d_out, int2* env, hipStream_t st) {
     using namespace edt;
-    return launch_dense3(nx, ny, nz, d_max, d_occ, d_out, d_out, d_out, env, st);
+    return launch_dense3(nx, ny, nz, d_max, d_occ,
+                         hull_ok(nx, ny, nz) ? (int32_t*)env : d_out, d_out, d_out, env, st);
 }
 
 // Device address of `scratch` on the current device, looked up once per
@@ -635,7 +963,7 @@ struct DenseLayout {
 
 bool dense_layout(int32_t nx, int32_t ny, int32_t nz, int64_t max_changes, DenseLayout* L) {
     if (!dense_ok(nx, ny, nz) || max_changes < 1 || max_changes > (1ll << 28)) return false;
-    const int64_t n = (int64_t)nx * ny * nz, nxc = (nx + 63) / 64;
+    const int64_t n = (int64_t)nx * ny * nz, nxc = row_words(nx);   // groups of 32 (or 64) columns
     int64_t ucap = 64;
     while (ucap < 2 * max_changes) ucap <<= 1;
     L->ucap = ucap;
@@ -718,7 +1046,7 @@ edt_status edt_dense_ctx_create(int32_t nx, int32_t ny, int32_t nz, int32_t d_ma
     c->mk.lz = (int32_t*)(b + L.lz);
     c->mk.tmp = (int32_t*)(b + L.env);   // long-row scratch of pass x (env is free then)
     hipStream_t st = (hipStream_t)stream;
-    const int64_t n = (int64_t)nx * ny * nz, nxc = (nx + 63) / 64;
+    const int64_t n = (int64_t)nx * ny * nz, nxc = row_words(nx);
     // empty map, no marks, empty dedupe table; then the field of the empty map
     auto fill = [&](int64_t off, int64_t words, int32_t v) {
         hipLaunchKernelGGL(k_dn_fill, dim3(grid_of((words + 255) / 256, 4096)), dim3(256), 0, st,
@@ -776,6 +1104,22 @@ edt_status edt_dense_ctx_update(edt_dense_ctx* c, const int32_t* d_xyz, const ui
                        ukeys, uvals, (const int32_t*)upos, c->mk);
     // listed rows (at most n), then the listed y and z groups
     const int32_t cap = c->d_max > 0 ? c->d_max * c->d_max : DINF;
+    if (hull_ok(nx, ny, nz)) {
+        const int nw = row_words(nx);
+        uint2* rec = (uint2*)g1;
+        with_row_lanes(nw, [&](auto lanes) {
+            constexpr int W = decltype(lanes)::value, RG = 256 / W;    // rows of a workgroup
+            hipLaunchKernelGGL(k_dense_rows_inc<W>, dim3(grid_of((n + RG - 1) / RG, 16384)),
+                               dim3(256), 0, st, nx, ny, nw, (const uint8_t*)occ, rec, c->mk);
+        });
+        hipLaunchKernelGGL((k_dense_hull<1, true>), dim3(grid_of((int64_t)nw * nz, 2048)),
+                           hull_threads(ny), hull_lds_bytes<uint16_t>(ny) + row_lds_bytes(ny), st, nx, ny, nz, nw,
+                           (const uint2*)rec, (const int32_t*)nullptr, g2, (int32_t)DINF, c->mk);
+        hipLaunchKernelGGL((k_dense_hull<2, true>), dim3(grid_of((int64_t)nw * ny, 8192)),
+                           hull_threads(nz), hull_lds_bytes<uint32_t>(nz), st, nx, ny, nz, nw,
+                           (const uint2*)nullptr, (const int32_t*)g2, sf, cap, c->mk);
+        return hipGetLastError() == hipSuccess ? EDT_OK : EDT_ERR_HIP;
+    }
     hipLaunchKernelGGL(k_dense_x<true>, dim3(grid_of(n, 65536)), dim3(64), 0, st, nx, ny, nz,
                        (const uint8_t*)occ, g1, c->mk);
     hipLaunchKernelGGL((k_dense_col<1, 16, true>), dim3(grid_of((int64_t)nxc * nz, 16384)),

@@ -1,0 +1,84 @@
+"""Dense transform by banded hulls (sides up to 2048 x 1024 x 1024) and the
+envelope form beyond them, against the oracle bit for bit at the edges of
+bands (32 rows), column groups (32 columns) and the two forms' border, with
+obstacles that make the columns' values random, convex, concave and flat; and
+the incremental form on the same shapes."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2105_04419_amd import DenseField, dense_global
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(31, 32, 31), (33, 64, 33), (64, 65, 32), (96, 31, 70), (2, 1024, 33), (2, 1025, 33),
+          (1024, 3, 34), (1025, 3, 34), (3, 2, 2048), (3, 2, 2049), (1, 1, 32), (1, 40, 1)]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _setup():
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    oracle.build(force=False)
+
+
+def draw(shape, kind):
+    nz, ny, nx = shape
+    rng = np.random.default_rng(nx + 3 * ny + 7 * nz + len(kind))
+    occ = np.zeros(shape, np.uint8)
+    z, y = np.meshgrid(np.arange(nz), np.arange(ny), indexing="ij")
+    if kind == "scattered":
+        occ[rng.random(shape) < 40.0 / occ.size] = 1
+    elif kind == "slope":              # the nearest x walks along the rows
+        occ[z, y, (y + z) % nx] = 1
+    elif kind == "bowl":               # distances along x grow with the square of y - mid
+        occ[z, y, np.minimum(nx - 1, (y - ny // 2) ** 2 // 8 + (z - nz // 2) ** 2 // 8)] = 1
+    else:                              # one wall, everything flat behind it
+        occ[:, :, nx // 2] = 1
+    occ.reshape(-1)[0] = 1
+    return occ
+
+
+def cu(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def ref(occ, d_max):
+    return oracle.edt_separable(occ, d_max) if d_max else oracle.edt_uncapped(occ)
+
+
+@pytest.mark.parametrize("kind", ["scattered", "slope", "bowl", "wall"])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_edges_match_the_oracle(shape, kind):
+    occ = draw(shape, kind)
+    for d_max in (0, 300):
+        got = dense_global(cu(occ), d_max).cpu().numpy()
+        assert np.array_equal(got, ref(occ, d_max)), (shape, kind, d_max)
+
+
+def test_occupancy_at_any_address():
+    occ = draw((5, 40, 77), "scattered")
+    flat = torch.zeros(occ.size + 64, dtype=torch.uint8, device="cuda")
+    for off in (1, 2, 7, 13):
+        v = flat[off:off + occ.size].view(occ.shape)
+        v.copy_(cu(occ))
+        assert np.array_equal(dense_global(v).cpu().numpy(), ref(occ, 0)), off
+
+
+@pytest.mark.parametrize("shape", [(33, 70, 65), (2, 1024, 40), (130, 33, 31), (1025, 2, 34)])
+def test_updates_match_the_oracle(shape):
+    nz, ny, nx = shape
+    rng = np.random.default_rng(sum(shape))
+    occ = draw(shape, "scattered")
+    f = DenseField((nx, ny, nz), 0, max_changes=64)
+    f.global_(cu(occ))
+    for _ in range(4):
+        xyz = np.stack([rng.integers(0, nx, 40), rng.integers(0, ny, 40),
+                        rng.integers(0, nz, 40)], 1).astype(np.int32)
+        xyz[:4] = np.argwhere(occ)[rng.integers(0, int(occ.sum()), 4)][:, ::-1]
+        st = (rng.random(40) < 0.4).astype(np.uint8)
+        for (x, y, z), v in zip(xyz, st):
+            occ[z, y, x] = v
+        f.update(cu(xyz), cu(st))
+        assert np.array_equal(f.field().cpu().numpy(), ref(occ, 0)), shape
+    assert f.error() == 0
