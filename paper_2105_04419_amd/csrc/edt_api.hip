@@ -26,8 +26,6 @@ struct edt_ctx {
     int ev_calls;       // calls to record
     int ev_used;        // calls recorded so far
     int ev_phase;       // phase bracketed by the events, or -1 for all of them
-    int cap;            // envelope ring capacity (entries per lane)
-    size_t env_lds;     // dynamic LDS bytes of the envelope passes
     int64_t tcap;       // tile hash capacity
     int64_t ucap;       // update hash capacity
     int64_t stats_host[C_N];
@@ -58,7 +56,7 @@ struct Layout {
 enum {
     O_TKEYS, O_TSLOTS, O_BKEY, O_OCC, O_G1, O_G2, O_S, O_BMAX, O_FLAGS, O_CNT,
     O_YI, O_ZI, O_SEED, O_DIRTY, O_XS, O_YS, O_NEWDIL, O_CHGA, O_CHGR,
-    O_UKEYS, O_UVALS, O_UPOS, O_DUMMY, O_DBLOCK, O_TOBST, O_TLIST, O_BMIN, O_TINFO, O_TFLAG, O_IIDX, O_ILIST, O_IC1, O_IC2, O_SCANXYZ, O_SCANST, O_SCANCNT, O_SCANOFF, O_SCANBLK, O_N
+    O_UKEYS, O_UVALS, O_UPOS, O_DBLOCK, O_TOBST, O_TLIST, O_BMIN, O_TINFO, O_TFLAG, O_IIDX, O_ILIST, O_IC1, O_IC2, O_SCANXYZ, O_SCANST, O_SCANCNT, O_SCANOFF, O_SCANBLK, O_N
 };
 
 bool valid_cfg(const edt_config* c) {
@@ -94,7 +92,7 @@ bool layout_of(const edt_config* c, Layout* L) {
         L->tcap * 8, L->tcap * 2048, mb * 8, mb * 64, mb * 1024, mb * 1024, mb * 1024, mb * 4,
         mb * 4, 64 * 4,
         mb * 4, mb * 4, mb * 4, mb * 4, mb * 4, mb * 4, mb * 4, mb * 64, mb * 64,
-        L->ucap * 8, L->ucap * 4, mc * 4, 256 * 256 * 4 + 1024, 1024,
+        L->ucap * 8, L->ucap * 4, mc * 4, 1024,
         L->tcap * 64, L->tcap * 4, mb * 4, L->tcap * 32, L->tcap * 4,
         mi ? mb * 4 : 0, mi * 4, mi * 1024, mi * 1024, mc * 12, mc, 256, mc * 8, (mc / 1024 + 1) * 16};
     int64_t o = 0;
@@ -143,7 +141,7 @@ inline int grid_for(int64_t work, int per, int cap) {
 
 // Pass along y (axis 1) or z (axis 2) over the item list of that axis.
 // d_max <= 64: windowed minimum (one instantiation per block radius);
-// larger radii: streaming lower envelope.
+// larger radii: lower envelopes by bands.
 template <int AXIS>
 void launch_win(const Grid& g, int grid, hipStream_t st, const int32_t* items, int counter,
                 uint32_t runflag) {
@@ -160,18 +158,28 @@ void launch_win(const Grid& g, int grid, hipStream_t st, const int32_t* items, i
     }
 }
 
+// Most blocks of a work item along an axis.
+inline int hull_item_blocks(const Grid& g, int axis) {
+    const int most = g.lrun + 2 * g.R, extent = axis == 1 ? g.nby : g.nbz;
+    return most < extent ? most : extent;
+}
+
 void launch_pass(edt_ctx* c, const Grid& g, int axis, hipStream_t st, const int32_t* items,
                  int counter, uint32_t runflag) {
     const int grid = grid_for(g.max_blocks, 1, 8192);
     if (g.R <= 8) {
         if (axis == 1) launch_win<1>(g, grid, st, items, counter, runflag);
         else launch_win<2>(g, grid, st, items, counter, runflag);
-    } else if (axis == 1) {
-        hipLaunchKernelGGL(k_pass_y, dim3(grid), dim3(64), c->env_lds, st, g, items, counter,
-                           runflag, c->cap);
     } else {
-        hipLaunchKernelGGL(k_pass_z, dim3(grid), dim3(64), c->env_lds, st, g, items, counter,
-                           runflag, c->cap);
+        // an item holds at most lrun + 2 R blocks, and no more than the extent
+        const int blocks = hull_item_blocks(g, axis);
+        const dim3 wg((hull_bands(8 * blocks) * HC + 63) & ~63);
+        if (axis == 1)
+            hipLaunchKernelGGL(k_pass_hull<1>, dim3(grid), wg, hull_item_lds<uint16_t>(blocks), st,
+                               g, items, counter, runflag, blocks);
+        else
+            hipLaunchKernelGGL(k_pass_hull<2>, dim3(grid), wg, hull_item_lds<uint32_t>(blocks), st,
+                               g, items, counter, runflag, blocks);
     }
 }
 
@@ -207,8 +215,8 @@ edt_status run_passes_global(edt_ctx* c, hipStream_t st) {
     } else {
         hipLaunchKernelGGL(k_items_tiles, dim3(grid_for(c->tcap, 1, 8192)), dim3(64), 0, st, g);
         mark(c, 3, st);
-        hipLaunchKernelGGL(k_pass_x, dim3(grid_for(mb, 1, 16384)), dim3(64), 0, st, g,
-                           (const int32_t*)nullptr, 0);
+        hipLaunchKernelGGL(k_pass_x_rows_wide, dim3(grid_for(c->tcap * 64, 1, 16384)), dim3(64), 0,
+                           st, g);
         mark(c, 4, st);
         launch_pass(c, g, 1, st, g.list_yi, (int)C_NYI, 0u);
         mark(c, 5, st);
@@ -228,11 +236,11 @@ edt_status dilate_region(edt_ctx* c, hipStream_t st) {
     const dim3 grid(grid_for(c->tcap, 1, 4096));
     switch (g.R) {
 #define EDT_DIL_CASE(r) \
-    case r: hipLaunchKernelGGL(k_tile_dilate<r>, grid, dim3(64), lds, st, g); break;
+    case r: hipLaunchKernelGGL((k_tile_dilate<r, 64>), grid, dim3(64), lds, st, g); break;
         EDT_DIL_CASE(1) EDT_DIL_CASE(2) EDT_DIL_CASE(3) EDT_DIL_CASE(4)
         EDT_DIL_CASE(5) EDT_DIL_CASE(6) EDT_DIL_CASE(7) EDT_DIL_CASE(8)
 #undef EDT_DIL_CASE
-        default: hipLaunchKernelGGL(k_tile_dilate<0>, grid, dim3(64), lds, st, g); break;
+        default: hipLaunchKernelGGL((k_tile_dilate<0, 256>), grid, dim3(256), lds, st, g); break;
     }
     LAUNCH_CHECK();
     return EDT_OK;
@@ -278,7 +286,6 @@ static void bind_workspace(edt_ctx* c, const edt_config* cfg, const Layout& L, c
     g.ukeys = (unsigned long long*)(b + L.off[O_UKEYS]);
     g.uvals = (int32_t*)(b + L.off[O_UVALS]);
     g.upos = (int32_t*)(b + L.off[O_UPOS]);
-    g.dummy = (uint32_t*)(b + L.off[O_DUMMY]);
     g.dblock = (uint16_t*)(b + L.off[O_DBLOCK]);
     g.tobst = (uint32_t*)(b + L.off[O_TOBST]);
     g.tlist = (int32_t*)(b + L.off[O_TLIST]);
@@ -373,25 +380,25 @@ edt_status edt_create(const edt_config* cfg, void* d_ws, int64_t ws_bytes, void*
     char* b = (char*)d_ws;
     bind_workspace(c, cfg, L, b);
     Grid& g = c->g;
-    c->cap = 2 * g.dmax + 4;   // live envelope sites never exceed 2 * d_max + 2
-    c->env_lds = (96 + 24) * 4 + (size_t)c->cap * 64 * 4;
-    // the envelope ring must fit the device's LDS per workgroup
-    int dev = 0, lds_max = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) !=
-            hipSuccess) {
-        free(c);
-        return EDT_ERR_HIP;
-    }
-    if ((int64_t)c->env_lds > lds_max) {
-        free(c);
-        return EDT_ERR_ARG;
-    }
-    if (c->env_lds > 65536) {
-        if (hipFuncSetAttribute((const void*)k_pass_y, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)c->env_lds) != hipSuccess ||
-            hipFuncSetAttribute((const void*)k_pass_z, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)c->env_lds) != hipSuccess) {
+    if (g.R > 8) {
+        // the envelopes of the longest work items must fit the device's LDS
+        int dev = 0, lds_max = 0;
+        const int ly = hull_item_lds<uint16_t>(hull_item_blocks(g, 1));
+        const int lz = hull_item_lds<uint32_t>(hull_item_blocks(g, 2));
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) !=
+                hipSuccess) {
+            free(c);
+            return EDT_ERR_HIP;
+        }
+        if (ly > lds_max || lz > lds_max) {
+            free(c);
+            return EDT_ERR_ARG;
+        }
+        if (hipFuncSetAttribute((const void*)k_pass_hull<1>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, ly) != hipSuccess ||
+            hipFuncSetAttribute((const void*)k_pass_hull<2>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, lz) != hipSuccess) {
             free(c);
             return EDT_ERR_HIP;
         }

@@ -664,7 +664,7 @@ __global__ void __launch_bounds__(1024, AXIS == 1 ? 8 : 5) k_dense_hull(int nx, 
         if (t < HC) h.nem[t] = 0u;
         // the band's rows into LDS, and the mask of those that can matter
         T* own = h.st + band * HB * HC + col;
-        HullMask mask(band, n);
+        HullMask mask(i0, 0, n - 1);
         uint32_t acc = 0u;                       // bit r: row r - 1
         if (AXIS == 1) {
             // each lane of the half wave fetches one record; all read them

@@ -34,7 +34,7 @@
 namespace edt {
 
 constexpr unsigned long long KEY_EMPTY = ~0ull;
-constexpr int LRUN = 16;        // longest y / z work item (blocks); Grid::lrun <= LRUN
+constexpr int LRUN = 64;        // longest y / z work item (blocks); Grid::lrun <= LRUN
 constexpr int32_t FINF = 1 << 28;
 
 enum : uint32_t {
@@ -106,7 +106,6 @@ struct Grid {
     uint16_t* ic1;           // [interior index][512] interior pass x (layout y + 8x + 64z),
                              // then the interior field (layout x + 8y + 64z)
     uint16_t* ic2;           // [interior index][512] interior pass y (layout z + 8x + 64y)
-    uint32_t* dummy;         // 256 x 256 words of write-only scratch rows
     uint16_t* dblock;        // one block of D values (stands for absent blocks)
 };
 

@@ -100,19 +100,20 @@ __host__ __device__ inline int32_t hull_f(uint32_t e) {
 
 // Rows of a band that can matter, taken in order: bit r of the mask is set
 // unless row r has no value, lies on or above the segment between its two
-// neighbours, is no lower than the next row already at output 0, or is still
-// no lower than the row before at the column's last output.  With the slopes
+// neighbours, is no lower than the next row already at the first output, or
+// is still no lower than the row before at the last one.  With the slopes
 // D(r) = F(r + 1) - F(r), a parabola is in charge from D(r - 1) / 2 to
 // D(r) / 2, so all of it is one comparison of neighbouring slopes clamped to
 // the outputs' range.  On the tunnel extent the z pass keeps 9.7 of 32 rows
 // (24.5 by the segment rule alone).  F = f + r^2 with r the row of the band,
 // HINF without a value and past the band's ends.
 struct HullMask {
-    int32_t lo, hi;              // slopes that are in charge before / after the column
+    int32_t lo, hi;              // slopes that are in charge before / after the outputs
     int32_t Fb = HINF, cp;       // the row before and the clamped slope up to it
     uint32_t bits = 0u;
-    __host__ __device__ HullMask(int band, int n)
-        : lo(-2 * band * HB), hi(2 * (n - 1) + 1 - 2 * band * HB), cp(clamped(0)) {}
+    // base: the band's first row; outputs first .. last are wanted
+    __host__ __device__ HullMask(int base, int first, int last)
+        : lo(2 * (first - base)), hi(2 * (last - base) + 1), cp(clamped(0)) {}
     __host__ __device__ int32_t clamped(int32_t D) const {
 #if defined(__HIP_DEVICE_COMPILE__)
         int32_t r;                                   // lo < hi: the median

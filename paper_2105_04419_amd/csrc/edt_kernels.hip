@@ -12,9 +12,8 @@
 // and never change the clamped result.  For d_max <= 64 the y and z passes
 // take the windowed minimum directly, branch-free on packed 16-bit pairs;
 // for larger radii they follow the lower envelope of parabolas (Felzenszwalb
-// & Huttenlocher, cited by the paper as the global transform), streamed with
-// one lane per row and a ring of the sites that can still reach the next
-// outputs.
+// & Huttenlocher, cited by the paper as the global transform), built by bands
+// of 32 rows in LDS (edt_hull.h).
 //
 // Incremental transform (Algorithm 1's raise and lower waves, at block
 // granularity): changed voxels are the wave centres; a block is on the lower
@@ -23,6 +22,7 @@
 // value (only such blocks can change); the g1/g2 intermediates are kept
 // current for every block and the marked blocks are recomputed exactly.
 #include "edt_dev.h"
+#include "edt_hull.h"
 #include "edt_win.h"
 
 namespace edt {
@@ -345,10 +345,13 @@ __global__ void __launch_bounds__(64) k_ingest_blocks_write(Grid g, const int32_
 // shifted by -R..R along x, then y, then z (separable Chebyshev dilation on
 // bit rows in LDS) and create the missing blocks of the dilated mask.  RT:
 // the block radius R as a constant (1 .. 8, one tile of neighbourhood, loops
-// unrolled), or 0 for any R read from the grid.
-template <int RT>
-__global__ void __launch_bounds__(64) k_tile_dilate(Grid g) {
-    extern __shared__ uint32_t sm[];
+// unrolled, one wave), or 0 for any R read from the grid: up to 9^3 tiles of
+// neighbourhood and 72^2 rows, which NT = 256 lanes share (33 -> 18 us at
+// R = 13, where the 128 tiles of a 512 x 512 x 128 extent leave half the CUs
+// without a workgroup).
+template <int RT, int NT>
+__global__ void __launch_bounds__(NT) k_tile_dilate(Grid g) {
+    extern __shared__ __align__(16) uint32_t sm[];
     const int R = RT > 0 ? RT : g.R, TR = RT > 0 ? 1 : (R + 7) >> 3, w = 2 * TR + 1,
               NN = w * w * w;
     const int E = 8 + 2 * R;                 // rows of the dilation window per axis
@@ -356,7 +359,7 @@ __global__ void __launch_bounds__(64) k_tile_dilate(Grid g) {
     uint8_t* s1 = (uint8_t*)(sm + NN * 16);  // [E][E]  x-dilated rows (y', z')
     uint8_t* s2 = s1 + E * E;                // [E][8]  y-dilated rows (z', y)
     uint8_t* dil = s2 + E * 8;               // [64]    result rows (y, z)
-    const int lane = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int64_t ntiles = g.cnt[C_NTILE];
     for (int64_t it = blockIdx.x; it < ntiles; it += gridDim.x) {
         const int t = g.tlist[it];
@@ -366,12 +369,15 @@ __global__ void __launch_bounds__(64) k_tile_dilate(Grid g) {
         // overlaps the dilation; only this workgroup writes them
         const int64_t e0 = (int64_t)t * 512 + 8 * lane;
         const int4 ta = *(const int4*)(g.tslots + e0), tb = *(const int4*)(g.tslots + e0 + 4);
-        for (int n = lane; n < NN; n += 64) {
+        for (int n = tid; n < NN; n += NT) {
             const int dx = n % w - TR, dy = (n / w) % w - TR, dz = n / (w * w) - TR;
             const int nt = (tx + dx < 0 || ty + dy < 0 || tz + dz < 0)
                                ? -1
                                : hpos(g.tkeys, g.tmask, pack_key(tx + dx, ty + dy, tz + dz));
-            for (int k = 0; k < 16; ++k) nmask[n * 16 + k] = nt >= 0 ? g.tobst[(int64_t)nt * 16 + k] : 0u;
+            const uint4* from = (const uint4*)(g.tobst + (int64_t)(nt >= 0 ? nt : 0) * 16);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                ((uint4*)nmask)[n * 4 + k] = nt >= 0 ? from[k] : make_uint4(0u, 0u, 0u, 0u);
             // the tile and its face neighbours for the tile passes
             // (n = dx + 1 + 3 (dy + 1) + 9 (dz + 1) when TR = 1)
             if (TR == 1) {
@@ -381,7 +387,7 @@ __global__ void __launch_bounds__(64) k_tile_dilate(Grid g) {
             }
         }
         __syncthreads();
-        for (int r = lane; r < E * E; r += 64) {            // x dilation
+        for (int r = tid; r < E * E; r += NT) {            // x dilation
             const int Y = r % E - R, Z = r / E - R;
             // the row across the w tiles along x: one mask byte per tile, bit
             // position X + 8 TR for X = -8 TR .. 8 + 8 TR - 1 (<= 72 bits)
@@ -429,7 +435,7 @@ __global__ void __launch_bounds__(64) k_tile_dilate(Grid g) {
             s1[r] = (uint8_t)d;
         }
         __syncthreads();
-        for (int r = lane; r < E * 8; r += 64) {            // y dilation
+        for (int r = tid; r < E * 8; r += NT) {            // y dilation
             const int y = r & 7, zp = r >> 3;
             uint32_t d = 0u;
 #pragma unroll
@@ -440,7 +446,7 @@ __global__ void __launch_bounds__(64) k_tile_dilate(Grid g) {
             s2[r] = (uint8_t)d;
         }
         __syncthreads();
-        {                                                   // z dilation, lane = y + 8z
+        if (tid < 64) {                                     // z dilation, lane = y + 8z
             const int y = lane & 7, z = lane >> 3;
             uint32_t d = 0u;
 #pragma unroll
@@ -454,63 +460,65 @@ __global__ void __launch_bounds__(64) k_tile_dilate(Grid g) {
         // create the dilated blocks that are missing; lane = row (y, z), its
         // 8 table entries are 8 lane .. 8 lane + 7.  One counter atomic per
         // tile; the new slots are contiguous.
-        const int y = lane & 7, z = lane >> 3;
-        const int by = 8 * ty + y, bz = 8 * tz + z;
-        const uint32_t d = dil[lane];
-        const int32_t ex[8] = {ta.x, ta.y, ta.z, ta.w, tb.x, tb.y, tb.z, tb.w};
-        const int nc = TR + w * (TR + w * TR);            // centre tile in nmask
-        const uint32_t ob = (nmask[nc * 16 + (lane >> 2)] >> (8 * (lane & 3))) & 0xffu;
-        uint32_t want = 0u;
+        if (tid < 64) {
+            const int y = lane & 7, z = lane >> 3;
+            const int by = 8 * ty + y, bz = 8 * tz + z;
+            const uint32_t d = dil[lane];
+            const int32_t ex[8] = {ta.x, ta.y, ta.z, ta.w, tb.x, tb.y, tb.z, tb.w};
+            const int nc = TR + w * (TR + w * TR);            // centre tile in nmask
+            const uint32_t ob = (nmask[nc * 16 + (lane >> 2)] >> (8 * (lane & 3))) & 0xffu;
+            uint32_t want = 0u;
 #pragma unroll
-        for (int x = 0; x < 8; ++x)
-            if (((d >> x) & 1u) && 8 * tx + x < g.nbx && by < g.nby && bz < g.nbz && ex[x] == -1)
-                want |= 1u << x;
-        const int c = __popc(want);
-        int incl = c;
+            for (int x = 0; x < 8; ++x)
+                if (((d >> x) & 1u) && 8 * tx + x < g.nbx && by < g.nby && bz < g.nbz && ex[x] == -1)
+                    want |= 1u << x;
+            const int c = __popc(want);
+            int incl = c;
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int v = __shfl_up(incl, o);
-            if (lane >= o) incl += v;
-        }
-        const int total = __shfl(incl, 63);
-        // obstacle blocks created here (block-list input) are counted as
-        // obstacle blocks; one 64-bit atomic advances both the block count
-        // (low word) and that count (high word)
-        const int nobst = wave_sum(__popc(want & ob));
-        if (total > 0) {
-            int base = 0;
-            if (lane == 0) {
-                static_assert(C_NDIL == C_NBLK + 1 && C_NBLK == 0, "adjacent counters");
-                const unsigned long long old = atomicAdd(
-                    (unsigned long long*)&g.cnt[C_NBLK],
-                    (unsigned long long)total | ((unsigned long long)nobst << 32));
-                base = (int)(uint32_t)old;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int v = __shfl_up(incl, o);
+                if (lane >= o) incl += v;
             }
-            base = __shfl(base, 0);
-            int slot = base + incl - c;
-#pragma unroll
-            for (int x = 0; x < 8; ++x) {
-                if (!((want >> x) & 1u)) continue;
-                const bool o = (ob >> x) & 1u;
-                if (slot < g.max_blocks) {
-                    g.tslots[e0 + x] = slot;
-                    g.bkey[slot] = pack_key(8 * tx + x, by, bz);
-                    g.flags[slot] = o ? F_DILATED : 0u;
-                } else {
-                    g.tslots[e0 + x] = -1;
-                    set_error(g, -3 /* EDT_ERR_CAPACITY */);
-                    g.cnt[C_ABORT] = 1;
+            const int total = __shfl(incl, 63);
+            // obstacle blocks created here (block-list input) are counted as
+            // obstacle blocks; one 64-bit atomic advances both the block count
+            // (low word) and that count (high word)
+            const int nobst = wave_sum(__popc(want & ob));
+            if (total > 0) {
+                int base = 0;
+                if (lane == 0) {
+                    static_assert(C_NDIL == C_NBLK + 1 && C_NBLK == 0, "adjacent counters");
+                    const unsigned long long old = atomicAdd(
+                        (unsigned long long*)&g.cnt[C_NBLK],
+                        (unsigned long long)total | ((unsigned long long)nobst << 32));
+                    base = (int)(uint32_t)old;
                 }
-                ++slot;
-            }
-            // zero the occupancy and change masks of the new slots
-            // [base, base + total), 16-byte stores (4 per mask of 64 bytes)
-            const int64_t lo = base, hi = min((int64_t)base + total, (int64_t)g.max_blocks);
-            const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
-            for (int64_t k = lo * 4 + lane; k < hi * 4; k += 64) {
-                ((uint4*)g.occ)[k] = zero;
-                ((uint4*)g.chg_add)[k] = zero;
-                ((uint4*)g.chg_rem)[k] = zero;
+                base = __shfl(base, 0);
+                int slot = base + incl - c;
+#pragma unroll
+                for (int x = 0; x < 8; ++x) {
+                    if (!((want >> x) & 1u)) continue;
+                    const bool o = (ob >> x) & 1u;
+                    if (slot < g.max_blocks) {
+                        g.tslots[e0 + x] = slot;
+                        g.bkey[slot] = pack_key(8 * tx + x, by, bz);
+                        g.flags[slot] = o ? F_DILATED : 0u;
+                    } else {
+                        g.tslots[e0 + x] = -1;
+                        set_error(g, -3 /* EDT_ERR_CAPACITY */);
+                        g.cnt[C_ABORT] = 1;
+                    }
+                    ++slot;
+                }
+                // zero the occupancy and change masks of the new slots
+                // [base, base + total), 16-byte stores (4 per mask of 64 bytes)
+                const int64_t lo = base, hi = min((int64_t)base + total, (int64_t)g.max_blocks);
+                const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
+                for (int64_t k = lo * 4 + lane; k < hi * 4; k += 64) {
+                    ((uint4*)g.occ)[k] = zero;
+                    ((uint4*)g.chg_add)[k] = zero;
+                    ((uint4*)g.chg_rem)[k] = zero;
+                }
             }
         }
         __syncthreads();
@@ -626,13 +634,89 @@ __global__ void __launch_bounds__(64) k_items_tiles(Grid g) {
     }
 }
 
+// g1 of a strip of 8 blocks along x (slots sl, -1 absent), one wave, lane =
+// row (y + 8z) of the blocks.  b: the rows' bytes; L: distance from the voxel
+// before the strip back to the nearest obstacle at or before it, R: from the
+// voxel after the strip to the nearest one at or after it.  Each lane sweeps
+// its row twice with a carried distance (left to right, then right to left
+// inside each block); a voxel's distance to the nearest obstacle along x is
+// the smaller of the two, capped at d_max.  The squared values are transposed
+// through LDS so that every lane stores 16 contiguous bytes of the y-major g1
+// block.
+template <bool F16>
+__device__ inline void x_strip(const Grid& g, const int32_t* sl, const uint32_t (&b)[8], uint32_t L,
+                               uint32_t R, uint4 (*tr)[72], int lane) {
+    const uint32_t dmax = (uint32_t)g.dmax;
+    // rc[j]: distance from the first voxel after central block j to
+    // the nearest obstacle at or after it
+    uint32_t rc[8];
+#pragma unroll
+    for (int j = 7; j >= 0; --j) {
+        rc[j] = R;
+        const uint32_t bj = b[j];
+        R = bj ? (uint32_t)(__ffs(bj) - 1) : R + 8u;
+    }
+    // least g1 of each block: 0 on a row holding an obstacle, else set
+    // by the end voxels (voxel 0 is nearest the left obstacle, voxel 7
+    // the right one).  lc: distance from the voxel before block j to
+    // the nearest obstacle at or before it.  The squares (<= 64^2) are
+    // reduced over the wave two blocks at a time, packed.
+    uint32_t bmins[4];
+    {
+        uint32_t lc = L, nsq[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t bj = b[j];
+            const uint32_t near = bj ? 0u : min(min(lc + 1u, rc[j] + 1u), dmax);
+            nsq[j] = near * near;
+            lc = bj ? (uint32_t)__clz(bj) - 24u : lc + 8u;
+        }
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+            bmins[h] = wave_reduce_pk_u16<false>(nsq[2 * h] | (nsq[2 * h + 1] << 16));
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const uint32_t bj = b[j];
+        const int bmin = (int)((bmins[j >> 1] >> (16 * (j & 1))) & 0xffffu);
+        uint32_t m[8], d[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) m[x] = (uint32_t)((int32_t)(bj << (31 - x)) >> 31);
+#pragma unroll
+        for (int x = 0; x < 8; ++x) { L = (L + 1u) & ~m[x]; d[x] = L; }
+        uint32_t r = rc[j];
+#pragma unroll
+        for (int x = 7; x >= 0; --x) {
+            r = (r + 1u) & ~m[x];
+            const uint32_t v = min(min(d[x], r), dmax);
+            d[x] = F16 ? (uint32_t)__builtin_bit_cast(unsigned short,
+                                                             (_Float16)(v * v))
+                              : v * v;
+        }
+        const int32_t slot = sl[j];
+        if (lane == 0 && slot >= 0) g.bmin1[slot] = (uint16_t)bmin;
+        // a block that is D everywhere is not stored: its readers see
+        // the block minimum D and take the shared D block instead
+        if (slot >= 0 && bmin < g.D) {
+            uint4* buf = tr[j & 1];
+            buf[lane + (lane >> 3)] = make_uint4(d[0] | (d[1] << 16), d[2] | (d[3] << 16),
+                                                 d[4] | (d[5] << 16), d[6] | (d[7] << 16));
+            __syncthreads();
+            // lane = x + 8z gathers column x of rows y + 8z, y = 0..7
+            const uint16_t* t16 = (const uint16_t*)buf + 72 * (lane >> 3) + (lane & 7);
+            uint32_t w[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                w[q] = (uint32_t)t16[16 * q] | ((uint32_t)t16[16 * q + 8] << 16);
+            *reinterpret_cast<uint4*>(g.g1 + (int64_t)slot * 512 + 8 * lane) =
+                make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    }
+}
+
 // pass X for the global transform: one wave per row of 8 blocks along x
-// inside a tile (64 per tile), lane = row (y + 8z) of the blocks.  Each lane
-// sweeps its row twice with a carried distance (left to right, then right to
-// left inside each block); a voxel's distance to the nearest obstacle along x
-// is the smaller of the two, capped at d_max (M = R <= 8 blocks of context on
-// each side cover d_max <= 64).  The squared values are transposed through
-// LDS so that every lane stores 16 contiguous bytes of the y-major g1 block.
+// inside a tile (64 per tile), with M = R <= 8 blocks of context on each side
+// (d_max <= 64).
 template <int M>
 __global__ void __launch_bounds__(64) k_pass_x_rows(Grid g) {
     constexpr int NB = 8 + 2 * M;
@@ -642,7 +726,6 @@ __global__ void __launch_bounds__(64) k_pass_x_rows(Grid g) {
     const int lane = threadIdx.x;
     const int64_t nrows = (int64_t)g.cnt[C_NTILE] * 64;
     const uint8_t* occ8 = (const uint8_t*)g.occ;
-    const uint32_t dmax = (uint32_t)g.dmax;
     for (int64_t it = blockIdx.x; it < nrows; it += gridDim.x) {
         const int32_t* ti = g.tinfo + (it >> 6) * 8;
         const int jy = (int)(it & 7), jz = (int)((it >> 3) & 7);
@@ -680,73 +763,75 @@ __global__ void __launch_bounds__(64) k_pass_x_rows(Grid g) {
             uint32_t L = FAR;
 #pragma unroll
             for (int k = 0; k < M; ++k) L = b[k] ? (uint32_t)__clz(b[k]) - 24u : L + 8u;
-            // rc[j]: distance from the first voxel after central block j to
-            // the nearest obstacle at or after it
-            uint32_t rc[8];
             uint32_t R = FAR;
 #pragma unroll
             for (int k = NB - 1; k >= M + 8; --k) R = b[k] ? (uint32_t)(__ffs(b[k]) - 1) : R + 8u;
+            uint32_t bc[8];
 #pragma unroll
-            for (int j = 7; j >= 0; --j) {
-                rc[j] = R;
-                const uint32_t bj = b[M + j];
-                R = bj ? (uint32_t)(__ffs(bj) - 1) : R + 8u;
-            }
-            // least g1 of each block: 0 on a row holding an obstacle, else set
-            // by the end voxels (voxel 0 is nearest the left obstacle, voxel 7
-            // the right one).  lc: distance from the voxel before block j to
-            // the nearest obstacle at or before it.  The squares (<= 64^2) are
-            // reduced over the wave two blocks at a time, packed.
-            uint32_t bmins[4];
-            {
-                uint32_t lc = L, nsq[8];
+            for (int j = 0; j < 8; ++j) bc[j] = b[M + j];
+            x_strip<win_f16(M)>(g, sl + M, bc, L, R, tr, lane);
+        }
+        __syncthreads();
+    }
+}
+
+// The same for larger radii (R = 9 .. 32 blocks of context): the context is
+// walked outwards four blocks at a time until every row has met an obstacle.
+// One wave per strip of 8 blocks instead of one per block looks its 2 R + 8
+// slots up once per strip (125 -> 19 us at d_max 100 on 512 x 512 x 128).
+__global__ void __launch_bounds__(64) k_pass_x_rows_wide(Grid g) {
+    constexpr uint32_t FAR = 1u << 20;
+    __shared__ int32_t sl[8 + 2 * 32];
+    __shared__ uint4 tr[2][72];
+    const int lane = threadIdx.x, R = g.R;
+    const int64_t nrows = (int64_t)g.cnt[C_NTILE] * 64;
+    const uint8_t* occ8 = (const uint8_t*)g.occ;
+    for (int64_t it = blockIdx.x; it < nrows; it += gridDim.x) {
+        const int t = g.tlist[it >> 6];
+        int tx, ty, tz;
+        unpack_key(g.tkeys[t], tx, ty, tz);
+        const int jy = (int)(it & 7), jz = (int)((it >> 3) & 7);
+        for (int i = lane; i < 8 + 2 * R; i += 64)
+            sl[i] = tile_rel_slot(g, t, tx, ty, tz, i - R, jy, jz);
+        __syncthreads();
+        bool any = false;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const uint32_t bj = b[M + j];
-                    const uint32_t near = bj ? 0u : min(min(lc + 1u, rc[j] + 1u), dmax);
-                    nsq[j] = near * near;
-                    lc = bj ? (uint32_t)__clz(bj) - 24u : lc + 8u;
-                }
-#pragma unroll
-                for (int h = 0; h < 4; ++h)
-                    bmins[h] = wave_reduce_pk_u16<false>(nsq[2 * h] | (nsq[2 * h + 1] << 16));
-            }
+        for (int j = 0; j < 8; ++j) any = any || sl[R + j] >= 0;
+        if (any) {
+            auto byte = [&](int i) -> uint32_t {
+                const int32_t s2 = sl[i];
+                return s2 >= 0 ? (uint32_t)occ8[(int64_t)s2 * 64 + lane] : 0u;
+            };
+            uint32_t b[8], orb = 0u;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const uint32_t bj = b[M + j];
-                const int bmin = (int)((bmins[j >> 1] >> (16 * (j & 1))) & 0xffffu);
-                uint32_t m[8], d[8];
+                b[j] = byte(R + j);
+                orb |= b[j];
+            }
+            uint32_t L = FAR, Rr = FAR;
+            for (int k = 0; k < R; k += 4) {
+                uint32_t l[4], r[4];
 #pragma unroll
-                for (int x = 0; x < 8; ++x) m[x] = (uint32_t)((int32_t)(bj << (31 - x)) >> 31);
-#pragma unroll
-                for (int x = 0; x < 8; ++x) { L = (L + 1u) & ~m[x]; d[x] = L; }
-                uint32_t r = rc[j];
-#pragma unroll
-                for (int x = 7; x >= 0; --x) {
-                    r = (r + 1u) & ~m[x];
-                    const uint32_t v = min(min(d[x], r), dmax);
-                    d[x] = win_f16(M) ? (uint32_t)__builtin_bit_cast(unsigned short,
-                                                                     (_Float16)(v * v))
-                                      : v * v;
+                for (int u = 0; u < 4; ++u) {
+                    l[u] = k + u < R ? byte(R - 1 - k - u) : 0u;
+                    r[u] = k + u < R ? byte(R + 8 + k + u) : 0u;
                 }
-                const int32_t slot = sl[M + j];
-                if (lane == 0 && slot >= 0) g.bmin1[slot] = (uint16_t)bmin;
-                // a block that is D everywhere is not stored: its readers see
-                // the block minimum D and take the shared D block instead
-                if (slot >= 0 && bmin < g.D) {
-                    uint4* buf = tr[j & 1];
-                    buf[lane + (lane >> 3)] = make_uint4(d[0] | (d[1] << 16), d[2] | (d[3] << 16),
-                                                         d[4] | (d[5] << 16), d[6] | (d[7] << 16));
-                    __syncthreads();
-                    // lane = x + 8z gathers column x of rows y + 8z, y = 0..7
-                    const uint16_t* t16 = (const uint16_t*)buf + 72 * (lane >> 3) + (lane & 7);
-                    uint32_t w[4];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        w[q] = (uint32_t)t16[16 * q] | ((uint32_t)t16[16 * q + 8] << 16);
-                    *reinterpret_cast<uint4*>(g.g1 + (int64_t)slot * 512 + 8 * lane) =
-                        make_uint4(w[0], w[1], w[2], w[3]);
+                for (int u = 0; u < 4; ++u) {
+                    if (L == FAR && l[u]) L = 8u * (k + u) + (uint32_t)__clz(l[u]) - 24u;
+                    if (Rr == FAR && r[u]) Rr = 8u * (k + u) + (uint32_t)(__ffs(r[u]) - 1);
                 }
+                if (__all(L != FAR && Rr != FAR)) break;
+            }
+            if (!__any(orb != 0u || L != FAR || Rr != FAR)) {
+                // no obstacle in the strip or its context
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int32_t slot = sl[R + j];
+                    if (lane == 0 && slot >= 0) g.bmin1[slot] = (uint16_t)g.D;
+                }
+            } else {
+                x_strip<false>(g, sl + R, b, L, Rr, tr, lane);
             }
         }
         __syncthreads();
@@ -754,8 +839,8 @@ __global__ void __launch_bounds__(64) k_pass_x_rows(Grid g) {
 }
 
 // ---------------------------------------------------------------------------
-// pass X: squared 1-D distance along x from the bits, clamped to D.  One wave
-// per block, lane = row (y + 8z).
+// pass X over a list of blocks (incremental transform): squared 1-D distance
+// along x from the bits, clamped to D.  One wave per block, lane = row (y + 8z).
 // ---------------------------------------------------------------------------
 __device__ inline void pass_x_body(const Grid& g, const int32_t* list, int list_counter,
                                    int64_t vb, int64_t vgrid, int32_t* nb) {
@@ -828,11 +913,6 @@ __device__ inline void pass_x_body(const Grid& g, const int32_t* list, int list_
     }
 }
 
-__global__ void __launch_bounds__(64) k_pass_x(Grid g, const int32_t* list, int list_counter) {
-    __shared__ int32_t nb[72];
-    pass_x_body(g, list, list_counter, blockIdx.x, gridDim.x, nb);
-}
-
 // Incremental transform: pass x over the xs list and the y / z work items
 // are independent, so they share one launch; the first nxw workgroups take
 // pass x.
@@ -845,93 +925,8 @@ __global__ void __launch_bounds__(64) k_upd_x_items(Grid g, int nxw) {
 }
 
 // ---------------------------------------------------------------------------
-// streaming lower envelope of parabolas, one row per lane
+// work items of the list-driven passes
 // ---------------------------------------------------------------------------
-// Sites are pushed in increasing position q with value f < D; outputs are
-// evaluated at i = q - dmax once every site that can reach i is in.  The
-// envelope is kept only on [next output, inf): the bottom site is removed
-// when the new site is no worse at the next output, and sites more than dmax
-// left of the output (values > D) are dropped.  The live sites then lie in a
-// window of 2*dmax + 2 positions, which bounds the ring.  The two sites at
-// each end of the envelope are mirrored in registers, so LDS is read only
-// when a site is popped from the top or passed at the bottom.
-struct Envelope {
-    uint32_t* ring;   // LDS, entry e of this lane at ring[e * 64 + lane]
-    int cap;          // ring capacity (entries)
-    int lane;
-    int n;            // live entries
-    int bp, tp;       // physical bottom / top index
-    uint32_t t0, t1;  // top, below top      (entry = position << 16 | value)
-    uint32_t b0, b1;  // bottom, above bottom
-
-    __device__ void init(uint32_t* r, int c, int l) {
-        ring = r; cap = c; lane = l; n = 0; bp = 0; tp = c - 1; t0 = t1 = b0 = b1 = 0u;
-    }
-    __device__ int inc(int p) const { return p + 1 == cap ? 0 : p + 1; }
-    __device__ int dec(int p) const { return p == 0 ? cap - 1 : p - 1; }
-    __device__ uint32_t at(int phys) const { return ring[phys * 64 + lane]; }
-    static __device__ int pos(uint32_t e) { return (int)(e >> 16); }
-    static __device__ int val(uint32_t e) { return (int)(e & 0xffffu); }
-
-    __device__ void push(int q, int f, int inext) {
-        const int kq = f + q * q;
-        while (n > 0) {
-            const int pt = pos(t0);
-            const int kt = val(t0) + pt * pt;
-            if (n == 1) {
-                // the only site: drop it if the new one is no worse on [inext, inf)
-                if (kq - kt <= 2 * inext * (q - pt)) {
-                    n = 0;
-                    tp = dec(bp);
-                }
-                break;
-            }
-            const int p0 = pos(t1);
-            const int k0 = val(t1) + p0 * p0;
-            // top is hidden when the new site meets t1 no later than top does
-            if ((kq - k0) * (pt - p0) <= (kt - k0) * (q - p0)) {
-                tp = dec(tp);
-                --n;
-                t0 = t1;
-                if (n >= 2) t1 = at(dec(tp));
-            } else {
-                break;
-            }
-        }
-        tp = inc(tp);
-        const uint32_t e = ((uint32_t)q << 16) | (uint32_t)f;
-        ring[tp * 64 + lane] = e;
-        ++n;
-        t1 = t0;
-        t0 = e;
-        if (n == 1) b0 = e;
-        else if (n == 2) b1 = e;
-    }
-
-    __device__ void advance() {
-        bp = inc(bp);
-        --n;
-        if (n >= 1) b0 = b1;
-        if (n >= 2) b1 = at(inc(bp));
-    }
-
-    // min over live sites of f + (i - p)^2, clamped to D
-    __device__ int eval(int i, int dmax, int D) {
-        while (n > 0 && pos(b0) < i - dmax) advance();
-        if (n == 0) return D;
-        int d0 = i - pos(b0);
-        int vb = val(b0) + d0 * d0;
-        while (n >= 2) {
-            const int d1 = i - pos(b1);
-            const int v1 = val(b1) + d1 * d1;
-            if (v1 > vb) break;
-            advance();
-            vb = v1;
-        }
-        return vb < D ? vb : D;
-    }
-};
-
 // Resolve the run of a y/z work item into LDS: sl[0 .. LRUN + 2R) holds the
 // slots of blocks start-R .. start+LRUN+R-1 along `axis` (-1 = absent).
 // Returns (hb, len, ha): halo blocks before, run length, halo blocks after.
@@ -941,7 +936,7 @@ __device__ inline void resolve_run(const Grid& g, int32_t* sl, uint8_t* mem, int
     const int R = g.R;
     const int nl = g.lrun + 2 * R;
     const int lane = threadIdx.x;
-    for (int i = lane; i < nl; i += 64) {
+    for (int i = lane; i < nl; i += (int)blockDim.x) {
         const int o = i - R;
         const int32_t s = axis == 1 ? find_block(g, bx, by + o, bz) : find_block(g, bx, by, bz + o);
         sl[i] = s;
@@ -971,172 +966,147 @@ __device__ inline void finish_run(const Grid& g, const int32_t* sl, int len, int
     if (lane < len) atomicAnd(&g.flags[sl[g.R + lane]], ~clear);
 }
 
-// The envelope passes walk the blocks of a work item two at a time with two
-// explicit input buffers (no register copies), and every step issues exactly
-// one global store (halo steps store to a per-wave scratch row), so the
-// memory operations form a fixed sequence and a step never waits for the
-// stores of the steps before it.
-//
-// pass Y: lane = x + 8z.  Reads g1 (layout (x + 8z) * 8 + y: one 16-byte
-// load per block and lane), writes g2 (layout (x + 8y) * 8 + z) and the
-// least g2 value of each output block (bmin2, read by the nearest-obstacle
-// query to tell blocks that are D everywhere).
-struct PassYItem {
-    const Grid& g;
-    const int32_t* sl;
-    Envelope& env;
-    int base, nb, o0, o1, qa, qb, dmax, D, lane, out_lane;
-    uint16_t* dummy;
-    int bm;
-
-    __device__ uint4 load(int j) const {
-        const int jj = j < nb ? j : nb - 1;
-        return ((const uint4*)g.g1)[(int64_t)sl[base + jj] * 64 + lane];
-    }
-    __device__ void block(uint4 cur, int j) {
-        const int jo = (j * 8 - dmax) >> 3;
-        const int32_t slo = (jo >= 0 && jo < nb) ? sl[base + jo] : -1;
-        const int32_t shi = (jo + 1 >= 0 && jo + 1 < nb) ? sl[base + jo + 1] : -1;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int q = 8 * j + k;
-            if (q >= qa && q < qb) {
-                const uint32_t wk = k < 2 ? cur.x : (k < 4 ? cur.y : (k < 6 ? cur.z : cur.w));
-                const int f = (int)((wk >> (16 * (k & 1))) & 0xffffu);
-                if (f < D) env.push(q, f, max(o0, q - dmax));
-            }
-            const int i = q - dmax;
-            const bool out = i >= o0 && i < o1;
-            int v = 0;
-            if (out) v = env.eval(i, dmax, D);
-            const int32_t slot = ((i >> 3) == jo) ? slo : shi;
-            uint16_t* dst = out ? g.g2 + (int64_t)slot * 512 + out_lane + 64 * (i & 7)
-                                : dummy + lane;
-            *dst = (uint16_t)v;
-            bm = min(bm, v);
-            if (((k - dmax) & 7) == 7) {          // the step that ends an output block
-                const int m = wave_min(bm);
-                uint16_t* bd = out ? g.bmin2 + slot : dummy + 64 + lane;
-                *bd = (uint16_t)m;
-                bm = D;
-            }
-        }
-    }
-};
-
-__global__ void __launch_bounds__(64) k_pass_y(Grid g, const int32_t* items, int item_counter,
-                                               uint32_t runflag, int cap) {
-    extern __shared__ uint32_t smem[];
-    int32_t* sl = (int32_t*)smem;                 // 96 entries
-    uint8_t* mem = (uint8_t*)(smem + 96);         // 96 bytes
-    uint32_t* ring = smem + 96 + 24;
-    const int lane = threadIdx.x;
-    const int64_t nit = g.cnt[item_counter];
-    const int R = g.R;
-    uint16_t* dummy = (uint16_t*)(g.dummy + (blockIdx.x & 255) * 64);
-    for (int64_t it = blockIdx.x; it < nit; it += gridDim.x) {
-        const int32_t s0 = items[it];
-        int bx, by, bz;
-        unpack_key(g.bkey[s0], bx, by, bz);
-        int hb, len, ha;
-        resolve_run(g, sl, mem, bx, by, bz, 1, runflag, hb, len, ha);
-        Envelope env;
-        env.init(ring, cap, lane);
-        const int nb = hb + len + ha;
-        const int o0 = 8 * hb, o1 = 8 * (hb + len);
-        PassYItem P{g, sl, env, R - hb, nb, o0, o1, max(0, o0 - g.dmax), min(8 * nb, o1 + g.dmax),
-                    g.dmax, g.D, lane, (lane & 7) * 8 + (lane >> 3), dummy, g.D};
-        const int jlo = P.qa >> 3, jhi = (o1 + g.dmax - 1) >> 3;
-        uint4 A = P.load(jlo), B = P.load(jlo + 1);
-        for (int j = jlo; j <= jhi; j += 2) {
-            P.block(A, j);
-            A = P.load(j + 2);
-            if (j + 1 > jhi) break;
-            P.block(B, j + 1);
-            B = P.load(j + 3);
-        }
-        finish_run(g, sl, len, 1, runflag);
-        __syncthreads();
-    }
+// ---------------------------------------------------------------------------
+// lower envelope along y or z for d_max > 64 (core in edt_hull.h)
+// ---------------------------------------------------------------------------
+// LDS of a work item of `blocks` blocks (run and halo): the envelope of 32
+// columns, then the slots, the block extrema and the membership bytes.
+template <class T>
+__host__ __device__ inline int hull_item_lds(int blocks) {
+    return hull_lds_bytes<T>(8 * blocks) + 128 * 4 + 128 * 4 + 128;
 }
 
-// pass Z: lane = x + 8y.  Reads g2 (one 16-byte load per block and lane),
-// writes s (uint16, layout x + 8y + 64z) and the per-block maximum.
-struct PassZItem {
-    const Grid& g;
-    const int32_t* sl;
-    Envelope& env;
-    int base, nb, o0, o1, qa, qb, dmax, D, lane;
-    int32_t* dummy;
-    int bm;
-
-    __device__ uint4 load(int j) const {
-        const int jj = j < nb ? j : nb - 1;
-        return ((const uint4*)g.g2)[(int64_t)sl[base + jj] * 64 + lane];
-    }
-    __device__ void block(uint4 cur, int j) {
-        const int jo = (j * 8 - dmax) >> 3;
-        const int32_t slo = (jo >= 0 && jo < nb) ? sl[base + jo] : -1;
-        const int32_t shi = (jo + 1 >= 0 && jo + 1 < nb) ? sl[base + jo + 1] : -1;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int q = 8 * j + k;
-            if (q >= qa && q < qb) {
-                const uint32_t wk = k < 2 ? cur.x : (k < 4 ? cur.y : (k < 6 ? cur.z : cur.w));
-                const int f = (int)((wk >> (16 * (k & 1))) & 0xffffu);
-                if (f < D) env.push(q, f, max(o0, q - dmax));
-            }
-            const int i = q - dmax;
-            const bool out = i >= o0 && i < o1;
-            int v = 0;
-            if (out) v = env.eval(i, dmax, D);
-            const int32_t slot = ((i >> 3) == jo) ? slo : shi;
-            uint16_t* dst =
-                out ? g.s + (int64_t)slot * 512 + lane + 64 * (i & 7) : (uint16_t*)dummy + lane;
-            *dst = (uint16_t)v;
-            bm = max(bm, v);
-            if (((k - dmax) & 7) == 7) {          // the step that ends an output block
-                const int m = wave_max(bm);
-                int32_t* bd = out ? g.bmax + slot : dummy + 64 + lane;
-                *bd = m;
-                bm = 0;
-            }
-        }
-    }
-};
-
-__global__ void __launch_bounds__(64) k_pass_z(Grid g, const int32_t* items, int item_counter,
-                                               uint32_t runflag, int cap) {
-    extern __shared__ uint32_t smem[];
-    int32_t* sl = (int32_t*)smem;
-    uint8_t* mem = (uint8_t*)(smem + 96);
-    uint32_t* ring = smem + 96 + 24;
-    const int lane = threadIdx.x;
+// Pass Y (AXIS 1: g1 -> g2 and the least g2 of each block) and pass Z (AXIS 2:
+// g2 -> s and the largest s of each block) over the work items: one workgroup
+// per item (a run of up to g.lrun output blocks and the blocks within R of
+// them), one lane per column and band of 32 rows, the item's 64 columns in two
+// halves of 32 (x = 4 h .. 4 h + 3 in pass Y, y = 4 h .. 4 h + 3 in pass Z, so
+// each half reads runs of 64 and writes runs of 64 bytes).  Values >= D are no
+// points.  g1 holds squares, so pass Y keeps 16-bit entries.  blocks: the most
+// blocks an item can have (LDS and workgroup are sized for it).
+//
+// At d_max 100 on 512 x 512 x 128 the passes take 109 and 84 us; with one lane
+// per column walking its rows in order they took 631 and 510 us (the ring of
+// live parabolas in LDS, two or three waves a SIMD waiting on it).  Runs of up
+// to 64 blocks: 32 repeat more of the halo (pass Y 140 us).  80 registers, for
+// six waves a SIMD; with 114 pass Y ran 174 us at runs of 32.
+template <int AXIS>
+__global__ void __launch_bounds__(1024, 6) k_pass_hull(Grid g, const int32_t* items, int item_counter,
+                                                   uint32_t runflag, int blocks) {
+    using T = typename std::conditional<AXIS == 1, uint16_t, uint32_t>::type;
+    extern __shared__ __align__(16) unsigned char lds[];
+    const HullLds<T> h = hull_lds<T>(lds, 8 * blocks);
+    int32_t* sl = (int32_t*)(lds + hull_lds_bytes<T>(8 * blocks));
+    int32_t* ext = sl + 128;
+    uint8_t* mem = (uint8_t*)(ext + 128);
+    const int t = threadIdx.x, col = t & (HC - 1), band = t / HC;
+    const int R = g.R, D = g.D;
     const int64_t nit = g.cnt[item_counter];
-    const int R = g.R;
-    int32_t* dummy = (int32_t*)(g.dummy + (blockIdx.x & 255) * 64);
+    const uint16_t* src = AXIS == 1 ? g.g1 : g.g2;
+    const uint16_t* bmin = AXIS == 1 ? g.bmin1 : g.bmin2;
+    uint16_t* dst = AXIS == 1 ? g.g2 : g.s;
     for (int64_t it = blockIdx.x; it < nit; it += gridDim.x) {
         const int32_t s0 = items[it];
         int bx, by, bz;
         unpack_key(g.bkey[s0], bx, by, bz);
         int hb, len, ha;
-        resolve_run(g, sl, mem, bx, by, bz, 2, runflag, hb, len, ha);
-        Envelope env;
-        env.init(ring, cap, lane);
-        const int nb = hb + len + ha;
-        const int o0 = 8 * hb, o1 = 8 * (hb + len);
-        PassZItem P{g, sl, env, R - hb, nb, o0, o1, max(0, o0 - g.dmax), min(8 * nb, o1 + g.dmax),
-                    g.dmax, g.D, lane, dummy, 0};
-        const int jlo = P.qa >> 3, jhi = (o1 + g.dmax - 1) >> 3;
-        uint4 A = P.load(jlo), B = P.load(jlo + 1);
-        for (int j = jlo; j <= jhi; j += 2) {
-            P.block(A, j);
-            A = P.load(j + 2);
-            if (j + 1 > jhi) break;
-            P.block(B, j + 1);
-            B = P.load(j + 3);
+        resolve_run(g, sl, mem, bx, by, bz, AXIS, runflag, hb, len, ha);
+        const int base = R - hb;                  // sl index of item block 0
+        const int n = hb + len + ha, nb = hull_bands(8 * n);
+        const int i0 = band * HB;
+        for (int half = 0; half < 2; ++half) {
+            // this lane's column of the source block (16 bytes each)
+            const int sc = AXIS == 1 ? 4 * half + (col >> 3) + 8 * (col & 7) : 32 * half + col;
+            if (t < HC) h.nem[t] = 0u;
+            uint32_t acc = 0u;
+            T* own = h.st + i0 * HC + col;
+            if (band < nb) {
+                HullMask mask(i0, 8 * hb, 8 * (hb + len) - 1);
+                uint4 v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int j = 4 * band + u;
+                    const int32_t slot = j < n ? sl[base + j] : -1;
+                    const bool full = slot >= 0 && (int)bmin[slot] < D;   // else D everywhere
+                    const uint32_t dd = (uint32_t)D | ((uint32_t)D << 16);
+                    v[u] = make_uint4(dd, dd, dd, dd);
+                    if (full) v[u] = ((const uint4*)src)[(int64_t)slot * 64 + sc];
+                }
+#pragma unroll
+                for (int r = 0; r < HB; ++r) {
+                    const uint32_t w = word_of(v[r >> 3], (r & 7) >> 1);
+                    const int f = (int)((r & 1) ? w >> 16 : w & 0xffffu);
+                    const uint32_t e = AXIS == 1
+                                           ? (uint32_t)(__builtin_amdgcn_sqrtf((float)f) + 0.5f)
+                                           : (uint32_t)f;
+                    mask.row(f >= D ? HINF : f + r * r, r == 0 ? 0u : 1u << (r - 1));
+                    own[r * HC] = (T)((e << 5) | (uint32_t)r);
+                }
+                mask.row(HINF, 1u << (HB - 1));
+                acc = mask.bits;
+            }
+            __syncthreads();
+            if (band < nb) {
+                const int k = hull_scan(own, acc);
+                h.rng[band * HC + col] = (uint16_t)(k << 8);
+                if (k) atomicOr(&h.nem[col], 1u << band);
+            }
+            __syncthreads();
+            for (int s = 1; s < nb; s <<= 1) {
+                const int lb = 2 * band * s;
+                if (lb + s < nb) {
+                    const uint32_t m = (1u << s) - 1u;
+                    const uint32_t dead = hull_merge(h, col, h.nem[col], m << lb, m << (lb + s));
+                    if (dead) atomicAnd(&h.nem[col], ~dead);
+                }
+                __syncthreads();
+            }
+            const uint32_t m = band < nb ? h.nem[col] : 0u;
+            if ((m >> band) & 1u) hull_enter(h, col, band, m);
+            __syncthreads();
+            if ((m >> band) & 1u) hull_cover(h, col, band, nb, m);
+            __syncthreads();
+            if (4 * band < hb + len && 4 * band + 4 > hb) {
+                HullCursor<T> c;
+                if (m) {
+                    const int b = h.start[band * HC + col];
+                    c.init(h, col, m, b, hull_start(h, col, b, i0));
+                }
+#pragma unroll 1
+                for (int j = max(4 * band, hb); j < min(4 * band + 4, hb + len); ++j) {
+                    int32_t res[HO];
+#pragma unroll
+                    for (int u = 0; u < HO; ++u) res[u] = D;
+                    if (m) c.take(h, col, 8 * j, res);
+                    const int32_t slot = sl[base + j];
+                    uint16_t* o = dst + (int64_t)slot * 512 + 32 * half + col;
+                    int x = res[0];
+#pragma unroll
+                    for (int u = 0; u < HO; ++u) {
+                        if (AXIS == 1) o[64 * u] = (uint16_t)res[u];
+                        else __builtin_nontemporal_store((uint16_t)res[u], &o[64 * u]);
+                        x = AXIS == 1 ? min(x, res[u]) : max(x, res[u]);
+                    }
+                    // extremum of the block: the half's, then both
+#pragma unroll
+                    for (int d = 16; d > 0; d >>= 1) {
+                        const int y = __shfl_xor(x, d, 32);
+                        x = AXIS == 1 ? min(x, y) : max(x, y);
+                    }
+                    if (col == 0) {
+                        if (half == 0) {
+                            ext[j] = x;
+                        } else if (AXIS == 1) {
+                            g.bmin2[slot] = (uint16_t)min(x, ext[j]);
+                        } else {
+                            g.bmax[slot] = max(x, ext[j]);
+                        }
+                    }
+                }
+            }
+            __syncthreads();
         }
-        finish_run(g, sl, len, 2, runflag);
+        finish_run(g, sl, len, AXIS, runflag);
         __syncthreads();
     }
 }

@@ -2,13 +2,14 @@
 envelope form beyond them, against the oracle bit for bit at the edges of
 bands (32 rows), column groups (32 columns) and the two forms' border, with
 obstacles that make the columns' values random, convex, concave and flat; and
-the incremental form on the same shapes."""
+the incremental form on the same shapes.  The sparse field's radii beyond 64
+use the same hulls over runs of blocks."""
 import numpy as np
 import pytest
 import torch
 
 import oracle
-from paper_2105_04419_amd import DenseField, dense_global
+from paper_2105_04419_amd import DenseField, Field, dense_global
 
 pytestmark = pytest.mark.gpu
 
@@ -81,4 +82,30 @@ def test_updates_match_the_oracle(shape):
             occ[z, y, x] = v
         f.update(cu(xyz), cu(st))
         assert np.array_equal(f.field().cpu().numpy(), ref(occ, 0)), shape
+    assert f.error() == 0
+
+
+@pytest.mark.parametrize("d_max", [65, 72, 129, 255])
+@pytest.mark.parametrize("shape", [(17, 9, 600), (9, 600, 20), (600, 20, 9), (40, 264, 33),
+                                   (8, 8, 8), (70, 70, 70)])
+def test_sparse_field_beyond_radius_64(shape, d_max):
+    # work items longer than a run (64 blocks), band and block remainders, and
+    # rows whose context spans several tiles; then updates through the lists
+    nz, ny, nx = shape
+    rng = np.random.default_rng(sum(shape) + d_max)
+    occ = np.zeros(shape, np.uint8)
+    occ.reshape(-1)[rng.integers(0, occ.size, 12)] = 1
+    f = Field((nx, ny, nz), d_max, max_changes=64)
+    f.global_(cu(occ))
+    assert np.array_equal(f.dense().cpu().numpy(), oracle.edt_separable(occ, d_max)), "global"
+    for step in range(2):
+        xyz = np.stack([rng.integers(0, nx, 12), rng.integers(0, ny, 12),
+                        rng.integers(0, nz, 12)], 1).astype(np.int32)
+        xyz[:4] = np.argwhere(occ)[:4][:, ::-1]
+        st = (rng.random(12) < 0.5).astype(np.uint8)
+        st[:4] = 0
+        for (x, y, z), v in zip(xyz, st):
+            occ[z, y, x] = v
+        f.update(cu(xyz), cu(st))
+        assert np.array_equal(f.dense().cpu().numpy(), oracle.edt_separable(occ, d_max)), step
     assert f.error() == 0
