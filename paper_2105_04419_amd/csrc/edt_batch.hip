@@ -2,13 +2,16 @@
 //
 // Every map goes through the same three separable passes as the single-map
 // transform (x from the occupancy bytes, then the windowed minimum along y
-// and z; d_max <= 64).  Maps are dense, so a block is addressed by its
-// position in the map's block grid and no region growth is needed.
+// and z; d_max <= 64).  Two neighbouring voxels of a row travel together: the
+// intermediates are rows of pairs, g1 two distances in 16 bits, g2 two values
+// in 32, rows padded to whole groups of four voxels (np pairs a row).
 //
 // Work items (per map, in map order; maps are ordered largest first):
-//   phase 0 (x)  a strip of 8 blocks along x at (by, bz)
-//   phase 1 (y)  a run of up to `lrun` blocks along y at (bx, bz)
-//   phase 2 (z)  a run of up to `lrun` blocks along z at (bx, by)
+//   phase 0 (x)  60 words of 32 voxels, in row order
+//   phase 1 (y)  64 pair columns (in order of z, x) and 8 lrun rows along y
+//   phase 2 (z)  64 pair columns (in order of y, x) and 8 lrun rows along z
+// The columns of an item run on over the ends of rows, so no lane is left
+// idle at a map's edge, whatever its sides.
 // FUSED runs all three phases of all maps in one cooperative persistent
 // launch: waves take items from a per-phase queue (chunks of `chunk` items
 // through one atomic, or a static stride), and a grid-wide barrier separates
@@ -23,6 +26,7 @@
 #include <string.h>
 
 #include "edt.h"
+#include "edt_row.h"
 #include "edt_win.h"
 
 namespace {
@@ -31,14 +35,34 @@ using namespace edt;
 
 struct MapDev {
     int nx, ny, nz;
-    int nbx, nby, nbz;
-    int nxr;                 // strips of 8 blocks along x
-    int pad;
+    int nby, nbz;            // rows along y / z in eights
+    int nw;                  // words of 32 voxels in a row
+    int np;                  // pairs in a row of g1 / g2 (even)
+    int ps;                  // pairs between rows y, y + 1 of g2
     int64_t occ_off;         // bytes into the occupancy input
     int64_t out_off;         // int32 elements into the output
-    int64_t blk_off;         // blocks into g1 / g2
-    int64_t pad2;            // (64 bytes: read as four 16-byte words)
+    int64_t pair_off;        // pairs into g1 ([z][y][pair])
+    int64_t pair2_off;       // pairs into g2 ([y][z][pair]; 64 bytes: read as four words)
 };
+
+// Pairs from one item of phase 2 to the next along a plane.  The items of
+// planes with rows of 32 or more overlap by 20 pairs (at least 31 voxels, as
+// at most two row ends of three unused values each lie in them), so that each
+// can store whole 128-byte lines (item_z).
+__host__ __device__ inline int z_step(const MapDev& m) { return m.nx >= 32 ? 44 : 64; }
+__host__ __device__ inline int z_chunks(const MapDev& m) {
+    const int cols = m.ny * m.np, step = z_step(m);
+    return cols <= 64 ? 1 : 1 + (cols - 64 + step - 1) / step;
+}
+
+// Work items of a map per phase.
+constexpr int XWORDS = 60;   // words a wave of phase 0 writes (two lanes of context a side)
+__host__ __device__ inline int64_t phase_items(const MapDev& m, int phase, int lrun) {
+    if (phase == 0) return ((int64_t)m.ny * m.nz * m.nw + XWORDS - 1) / XWORDS;
+    if (phase == 1)
+        return (((int64_t)m.nz * m.np + 63) / 64) * ((m.nby + lrun - 1) / lrun);
+    return (int64_t)z_chunks(m) * ((m.nbz + lrun - 1) / lrun);
+}
 
 struct BArgs {
     const MapDev* maps;
@@ -48,66 +72,27 @@ struct BArgs {
     int64_t icap;
     const uint8_t* occ;
     int32_t* out;
-    uint8_t* g1;             // distance along x, min(d, d_max) (8 bits per voxel)
-    uint16_t* g2;
-    const uint16_t* dblock;
-    const uint8_t* dblock8;  // g1 of blocks beyond a map: d_max everywhere
-    uint32_t* dummy;
+    uint16_t* g1;            // distances along x, min(d, d_max), a byte per voxel of the pair
+    uint32_t* g2;            // two 16-bit values in the window's representation
     int n_maps;
-    int dmax, D;
+    int dmax, D, M;
     int lrun, chunk, schedule;
 };
 
-
-// g1 of block (bx, by, bz): this lane's 8 bytes (the 8 values along y of
-// column x + 8z), or the d_max block beyond the map.
-__device__ inline const uint2* blk_ptr8(const uint8_t* arr, const MapDev& m, int bx, int by,
-                                        int bz, const uint8_t* dblock8, int lane) {
-    if (bx < 0 || by < 0 || bz < 0 || bx >= m.nbx || by >= m.nby || bz >= m.nbz)
-        return (const uint2*)dblock8 + lane;
-    const int64_t b = m.blk_off + ((int64_t)bz * m.nby + by) * m.nbx + bx;
-    return (const uint2*)arr + b * 64 + lane;
-}
-
-// Eight 8-bit distances (at most 64) to their squares in the window's
-// representation, packed in 16-bit pairs in order.  v_perm builds each pair
-// with the high bytes 0x64 (F16: 0x64nn is the binary16 of 1024 + n, exact,
-// so subtracting 1024 leaves n, and n^2 <= 1600 is exact) or zero (integer
-// squares <= 4096).
+// Two 8-bit distances (at most 64) to their squares in the window's
+// representation.  v_perm gives each half the high byte 0x64 (F16: 0x64nn is
+// the binary16 of 1024 + n, exact, so subtracting 1024 leaves n, and n^2 <=
+// 1600 is exact) or zero (integer squares <= 4096).
 template <bool F16>
-__device__ inline uint4 g1_squares(uint2 w) {
-    const uint32_t hi = F16 ? 0x64646464u : 0u;
-    auto pair = [&](uint32_t word, uint32_t k) -> uint32_t {
-        const uint32_t sel = k | (4u << 8) | ((k + 1u) << 16) | (4u << 24);
-        const uint32_t x = __builtin_amdgcn_perm(hi, word, sel);
-        if (F16) {
-            const h16x2 f = as_h16x2(as_u16x2(x)) - (h16x2){(_Float16)1024, (_Float16)1024};
-            return as_u32(as_u16x2(f * f));
-        }
-        const u16x2 v = as_u16x2(x);
-        return as_u32(v * v);
-    };
-    return make_uint4(pair(w.x, 0u), pair(w.x, 2u), pair(w.y, 0u), pair(w.y, 2u));
+__device__ inline uint32_t pair_squares(uint32_t w) {
+    const uint32_t x = __builtin_amdgcn_perm(F16 ? 0x64646464u : 0u, w, 0x04010400u);
+    if (F16) {
+        const h16x2 f = as_h16x2(as_u16x2(x)) - (h16x2){(_Float16)1024, (_Float16)1024};
+        return as_u32(as_u16x2(f * f));
+    }
+    const u16x2 v = as_u16x2(x);
+    return as_u32(v * v);
 }
-
-// phase 0: distance along x for a strip of 8 blocks.  The wave walks
-// the strip's 64 rows (y, z); for each row the lanes read the window
-// x = 8 (bx0 - M) .. 8 (bx0 + 8 + M) - 1 with coalesced byte loads (64 + 16M
-// bytes, up to three per lane), ballots make it a bit string, which goes
-// through LDS to lane r.  Then
-// every lane holds its own row and sweeps it with carried distances, in
-// packed 16-bit pairs: blocks j and j + 4 of the strip at once (the carry
-// into block 4 comes from the bits of blocks 0..3, the carry out of block 3
-// from those of blocks 4..7), about 6 operations per voxel; M = ceil(d_max /
-// 8) blocks of context cover d_max.  Results, min(d, d_max) in one byte
-// (phase 1 squares them as it loads them: half the bytes of a stored
-// square), gather in LDS in the g1 block layout (y + 8x + 64z), two blocks
-// at a time, and leave as 8-byte stores.
-// LDS of item_x: the row words of the window (64 rows of up to three 64-bit
-// words), which two result blocks (2 x 512 bytes) reuse once they are read;
-// the workgroup's share is sized at launch, one slice per wave
-constexpr size_t XBYTES_PER_WAVE = 2 * 512 * sizeof(uint16_t);
-extern __shared__ __align__(16) uint16_t xlds[];
 
 // each 16-bit half of t: all ones if its bit 15 is set, else zero.  Written
 // as the instruction itself: as plain code the compiler turns the masks into
@@ -119,212 +104,369 @@ __device__ inline uint32_t pk_sign_mask(uint32_t t) {
     return r;
 }
 
-template <int M>
-__device__ void item_x(const BArgs& a, const MapDev& m, int li) {
-    constexpr int NBYTES = 64 + 16 * M;          // window bytes per row
-    constexpr int NWIN = (NBYTES + 63) / 64;     // 64-bit words of the window
-    // rows whose loads are in flight together (32 measured fastest: 16 keeps
-    // fewer loads in flight, 64 needs 143 registers)
-    constexpr int RB = 32;
-    constexpr int NB = 8 + 2 * M;                // window blocks
-    uint16_t* buf = xlds + (threadIdx.x >> 6) * (XBYTES_PER_WAVE / sizeof(uint16_t));
+// phase 0: distances along x.  One lane per word of 32 voxels of a row, words
+// in row order; a distance above 64 does not count, so the two words on either
+// side, from the lanes beside, are all the context there is, and a wave's
+// outer two lanes a side are context only.  The words of a wave are one run of
+// the map's bytes: it is read in aligned 16-byte pieces, which become bits in
+// LDS, and each lane cuts its word out of them.  The lane sweeps the word with
+// carried distances in packed 16-bit halves, voxels x and x + 16 at once, and
+// min(d, d_max), a byte per voxel, goes out through LDS in whole lines.
+// (Loads and stores of 32 bytes a lane at any alignment keep the address unit
+// busy 90% of the time.)  Bound by memory and issue about equally: 104 us for
+// 206 M voxels (1 byte read and 1 written each); a byte load and a ballot per
+// row took 185 us.
+constexpr int XBITS = 144;                     // 16-bit pieces of a wave's bits
+constexpr int XSLICE = XBITS * 2 + 64 * 32;    // LDS bytes of a wave
+extern __shared__ __align__(16) unsigned char xlds[];
+
+__device__ inline void item_x(const BArgs& a, const MapDev& m, int li) {
+    unsigned char* slice = xlds + (threadIdx.x >> 6) * XSLICE;
+    uint16_t* bits = (uint16_t*)slice;
+    uint32_t* outw = (uint32_t*)(slice + XBITS * 2);
     const int lane = threadIdx.x & 63;
-    const int nx = m.nx, ny = m.ny, nz = m.nz;
-    const int bx0 = 8 * (li % m.nxr);
-    const int rest = li / m.nxr;
-    const int by = rest % m.nby, bz = rest / m.nby;
-    const int xs = 8 * (bx0 - M);
-    // loads always hit a voxel of the map (clamped); bytes outside it are
-    // dropped afterwards
-    uint32_t xo[NWIN];
-    bool vx[NWIN];
+    const int64_t words = (int64_t)m.ny * m.nz * m.nw;
+    const int64_t i0 = (int64_t)li * XWORDS - 2, i = i0 + lane;
+    const bool ok = i >= 0 && i < words;
+    const int64_t ic = i < 0 ? 0 : (i < words ? i : words - 1);
+    const int row = (int)((uint32_t)ic / (uint32_t)m.nw);
+    const int w = (int)(ic - (int64_t)row * m.nw);
+    const int64_t total = (int64_t)m.ny * m.nz * m.nx;
+    const int64_t at = (int64_t)row * m.nx + 32 * w;          // byte of the map
+    const uint8_t* map = a.occ + m.occ_off;
+    // the wave's bytes start at lane 0's word; rounded down to 16 in memory
+    const int64_t at0 = __shfl(at, 0);
+    const int head = (int)((uintptr_t)(map + at0) & 15);
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int w = 0; w < NWIN; ++w) {
-        const int x = xs + 64 * w + lane;
-        vx[w] = 64 * w + lane < NBYTES && x >= 0 && x < nx;
-        xo[w] = (uint32_t)min(max(x, 0), nx - 1);
-    }
-    const uint8_t* base = a.occ + m.occ_off;
-    const int64_t zst = (int64_t)ny * nx;
-    // the rows' window words (row r, word w at rowbits[NWIN r + w]) share the
-    // buffer: they are read back before any result is written
-    static_assert(NWIN * 64 * sizeof(unsigned long long) <= XBYTES_PER_WAVE, "row words");
-    unsigned long long* rowbits = (unsigned long long*)buf;
-#pragma unroll
-    for (int r0 = 0; r0 < 64; r0 += RB) {
-        uint32_t bt[RB][NWIN];
-#pragma unroll
-        for (int k = 0; k < RB; ++k) {
-            const int r = r0 + k;
-            const int Y = min(8 * by + (r & 7), ny - 1), Z = min(8 * bz + (r >> 3), nz - 1);
-            const uint8_t* row = base + Z * zst + (int64_t)Y * nx;
-#pragma unroll
-            for (int w = 0; w < NWIN; ++w) bt[k][w] = row[xo[w]];
+    for (int k = 0; k < 3; ++k) {
+        const int c = 64 * k + lane;                          // piece: bytes 16 c - head on
+        if (c >= 130) continue;
+        const int64_t b = at0 - head + 16 * c;
+        uint32_t v = 0u;
+        if (b >= 0 && b + 16 <= total) {
+            const uint4 q = *(const uint4*)(map + b);
+            v = bytes8_bits(q.x, q.y) | (bytes8_bits(q.z, q.w) << 8);
+        } else if (b + 16 > 0 && b < total) {                 // an end of the map
+            for (int k2 = 0; k2 < 16; ++k2)
+                if (b + k2 >= 0 && b + k2 < total && map[b + k2]) v |= 1u << k2;
         }
+        bits[c] = (uint16_t)v;
+    }
+    __builtin_amdgcn_wave_barrier();
+    const int bit = (int)(at - at0) + head;
+    const uint32_t* b32 = (const uint32_t*)bits + (bit >> 5);
+    const int here = min(32, m.nx - 32 * w);                  // voxels of the word in the row
+    uint32_t word = __builtin_amdgcn_alignbit(b32[1], b32[0], bit & 31) &
+                    (here == 32 ? ~0u : (1u << here) - 1u);
+    if (!ok) word = 0u;
+    // words w - 2, w - 1, w + 1, w + 2 of the row (0 past its ends)
+    const uint32_t l2 = __shfl_up(word, 2), l1 = __shfl_up(word, 1);
+    const uint32_t r1 = __shfl_down(word, 1), r2 = __shfl_down(word, 2);
+    // distances from the last voxel before the word back to the nearest
+    // obstacle at or before it, and from the first one after it onwards
+    constexpr uint32_t FAR = 0x100u;
+    const uint32_t pl = w > 0 ? l1 : 0u, pl2 = w > 1 ? l2 : 0u;
+    const uint32_t pr = w + 1 < m.nw ? r1 : 0u, pr2 = w + 2 < m.nw ? r2 : 0u;
+    const uint32_t L = pl ? (uint32_t)__clz(pl) : (pl2 ? 32u + (uint32_t)__clz(pl2) : FAR);
+    const uint32_t R =
+        pr ? (uint32_t)__ffs(pr) - 1u : (pr2 ? 32u + (uint32_t)__ffs(pr2) - 1u : FAR);
+    // the same from voxel 15 back and from voxel 16 on
+    const uint32_t wl = word & 0xffffu, wh = word >> 16;
+    const uint32_t L16 = wl ? (uint32_t)__clz(wl) - 16u : L + 16u;
+    const uint32_t R16 = wh ? (uint32_t)__ffs(wh) - 1u : R + 16u;
+    const u16x2 one = {1, 1};
+    const u16x2 dmp = {(unsigned short)a.dmax, (unsigned short)a.dmax};
+    uint32_t mk[16];
+    u16x2 d[16];
 #pragma unroll
-        for (int k = 0; k < RB; ++k) {
-            const int r = r0 + k;
-            const bool rok = 8 * by + (r & 7) < ny && 8 * bz + (r >> 3) < nz;
+    for (int x = 0; x < 16; ++x) {
+        // bits x and x + 16 into bit 15 of the two halves: all ones where set
+        mk[x] = pk_sign_mask(as_u32(as_u16x2(word) << (u16x2){(unsigned short)(15 - x),
+                                                              (unsigned short)(15 - x)}));
+    }
+    uint32_t c = L | (L16 << 16);
 #pragma unroll
-            for (int w = 0; w < NWIN; ++w) {
-                // every lane stores the same word (no per-lane branch)
-                rowbits[NWIN * r + w] =
-                    __builtin_amdgcn_ballot_w64(rok && vx[w] && bt[k][w] != 0u);
+    for (int x = 0; x < 16; ++x) {
+        c = as_u32(as_u16x2(c) + one) & ~mk[x];
+        d[x] = as_u16x2(c);
+    }
+    c = R16 | (R << 16);
+#pragma unroll
+    for (int x = 15; x >= 0; --x) {
+        c = as_u32(as_u16x2(c) + one) & ~mk[x];
+        d[x] = __builtin_elementwise_min(__builtin_elementwise_min(d[x], as_u16x2(c)), dmp);
+    }
+    // voxels 4 q .. 4 q + 3 from the low halves, 16 more on from the high ones
+    uint32_t v[8];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t e0 = as_u32(d[4 * q]), e1 = as_u32(d[4 * q + 1]);
+        const uint32_t e2 = as_u32(d[4 * q + 2]), e3 = as_u32(d[4 * q + 3]);
+        // bytes 0 and 2 of two words: lo0 lo1 hi0 hi1
+        const uint32_t p = __builtin_amdgcn_perm(e1, e0, 0x06020400u);
+        const uint32_t r = __builtin_amdgcn_perm(e3, e2, 0x06020400u);
+        v[q] = (p & 0xffffu) | (r << 16);
+        v[q + 4] = (p >> 16) | (r & 0xffff0000u);
+    }
+    // the row's share of the word, in words of four voxels; the wave's words
+    // (lanes 2 .. 61) follow each other in g1
+    const bool mine = ok && lane >= 2 && lane < 62;
+    const int64_t o = ((m.pair_off + (int64_t)row * m.np) >> 1) + 8 * w;
+    const int left = mine ? min(8, m.np / 2 - 8 * w) : 0;
+    const int64_t o0 = __shfl(o, 2);
+    const int n = (int)min((int64_t)li * XWORDS + XWORDS, words) - 1 - (int)i0;   // last lane
+    const int count = (int)(__shfl(o + left, n) - o0);
+    uint32_t* lo = outw + (int)(o - o0);
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        if (q < left) lo[q] = v[q];
+    __builtin_amdgcn_wave_barrier();
+    uint32_t* dst = (uint32_t*)a.g1 + o0;
+    for (int k = lane; k < count; k += 64) dst[k] = outw[k];
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Windowed minimum of one pair column per lane, rows first .. first + 8 steps
+// - 1 of a column (both values of a pair at once, in packed 16 bits):
+//   out(i) = min over |k| <= 8 M - 1 of in(i + k) + k^2.
+// load(i, v): rows i .. i + 7 as stored (callers give rows past the column's
+// ends d_max or D); conv turns one into the window's representation; emit(r,
+// acc): outputs of rows r .. r + 7.  Eight outputs a step, offsets outward.  The 24 rows
+// within 8 of the outputs stay in registers, the next 8 on their way; rows
+// further off are read when some output is still larger than the square of
+// their offset, which dense maps seldom need: so the radius costs no
+// registers.
+template <bool F16, class Load, class Conv, class Emit>
+__device__ inline void column_min(int first, int steps, int M, Load&& load, Conv&& conv,
+                                  Emit&& emit) {
+    u16x2 P[24];                                 // rows r - 8 .. r + 15
+    {
+        uint32_t v[3][8];
+#pragma unroll
+        for (int h = 0; h < 3; ++h) load(first - 8 + 8 * h, v[h]);
+#pragma unroll
+        for (int q = 0; q < 24; ++q) P[q] = as_u16x2(conv(v[q >> 3][q & 7]));
+    }
+    // largest of the outputs (binary16 patterns order like their values)
+    auto over = [&](const u16x2* acc, uint32_t lim) {
+        const u16x2 mx = max8<F16>(acc);
+        return __any((uint32_t)mx.x > lim || (uint32_t)mx.y > lim) != 0;
+    };
+    auto bits = [](uint32_t n) -> uint32_t {     // n <= 2048, in the window's representation
+        return F16 ? (uint32_t)__builtin_bit_cast(unsigned short, (_Float16)(int)n) : n;
+    };
+    // offsets t0 .. t1 - 1 (added to 8 G) of the eight outputs: A[8 + o - t]
+    // and B[o + t] are the rows at -(8 G + t) and +(8 G + t); sq(t) their
+    // squares
+    auto offsets = [&](u16x2* acc, const u16x2* A, const u16x2* B, int t0, int t1, auto&& sq) {
+#pragma unroll
+        for (int t = t0; t < t1; ++t) {
+            const uint32_t k2 = sq(t);
+            const u16x2 kk = {(unsigned short)k2, (unsigned short)k2};
+#pragma unroll
+            for (int o = 0; o < 8; ++o) {
+                const u16x2 c = __builtin_elementwise_min(A[8 + o - t], B[o + t]);
+                if (F16)
+                    acc[o] = as_u16x2(__builtin_elementwise_minimum(as_h16x2(acc[o]),
+                                                                    as_h16x2(c) + as_h16x2(kk)));
+                else
+                    acc[o] = __builtin_elementwise_min(acc[o], c + kk);
             }
         }
-    }
-    // window words of row `lane` (lo and hi halves)
-    uint32_t rlo[NWIN], rhi[NWIN];
+    };
+    for (int s = 0; s < steps; ++s) {
+        const int r = first + 8 * s;
+        uint32_t N[8];
+        load(r + 16, N);
+        u16x2 acc[8];
 #pragma unroll
-    for (int w = 0; w < NWIN; ++w) {
-        const unsigned long long W = rowbits[NWIN * lane + w];
-        rlo[w] = (uint32_t)W;
-        rhi[w] = (uint32_t)(W >> 32);
-    }
-    // bytes of the row: block k of the window (k = 0 .. NB - 1)
-    uint32_t b[NB];
+        for (int o = 0; o < 8; ++o) acc[o] = P[8 + o];
+        auto near2 = [](int t) -> uint32_t { return F16 ? f16_bits(t * t) : (uint32_t)(t * t); };
+        offsets(acc, P, P + 8, 1, 4, near2);
+        if (over(acc, near2(4))) {
+            offsets(acc, P, P + 8, 4, 8, near2);
+            if (M > 1 && over(acc, near2(8))) {
+                u16x2 A[16], B[16];
 #pragma unroll
-    for (int k = 0; k < NB; ++k) {
-        const int w = k >> 3, h = (k >> 2) & 1, sh = 8 * (k & 3);
-        b[k] = ((h ? rhi[w] : rlo[w]) >> sh) & 0xffu;
-    }
-    // "no obstacle": beyond every radius, and small enough that the carried
-    // distances (at most 16 (M + 8) more) stay within 16 bits
-    constexpr uint32_t FAR = 0x3000u;
-    const uint32_t dmax = (uint32_t)a.dmax;
-    // distance from the last voxel before the strip back to the nearest obstacle
-    uint32_t L = FAR;
+                for (int q = 0; q < 16; ++q) {
+                    A[q] = P[q];
+                    B[q] = P[8 + q];
+                }
+#pragma unroll 1
+                for (int G = 1; G < M; ++G) {
+                    uint32_t a8[8], b8[8];
+                    load(r - 8 * G - 8, a8);
+                    load(r + 8 * G + 8, b8);
 #pragma unroll
-    for (int k = 0; k < M; ++k) L = b[k] ? (uint32_t)__clz(b[k]) - 24u : L + 8u;
-    // the same from the last voxel of strip block 3
-    const uint32_t W0 = b[M] | (b[M + 1] << 8) | (b[M + 2] << 16) | (b[M + 3] << 24);
-    const uint32_t L4 = W0 ? (uint32_t)__clz(W0) : L + 32u;
-    // rc[j]: distance from the first voxel after strip block j to the nearest
-    // obstacle at or after it
-    uint32_t rc[8];
-    uint32_t R = FAR;
+                    for (int u = 0; u < 8; ++u) {
+                        A[8 + u] = A[u];
+                        B[u] = B[8 + u];
+                        A[u] = as_u16x2(conv(a8[u]));
+                        B[8 + u] = as_u16x2(conv(b8[u]));
+                    }
+                    // no lane can gain when its least row plus (8 G)^2 is no
+                    // less than its largest output
+                    u16x2 lb = B[0];
 #pragma unroll
-    for (int k = NB - 1; k >= M + 8; --k) R = b[k] ? (uint32_t)(__ffs(b[k]) - 1) : R + 8u;
+                    for (int q = 1; q < 15; ++q) lb = __builtin_elementwise_min(lb, B[q]);
 #pragma unroll
-    for (int j = 7; j >= 0; --j) {
-        rc[j] = R;
-        const uint32_t bj = b[M + j];
-        R = bj ? (uint32_t)(__ffs(bj) - 1) : R + 8u;
-    }
-    const int rofs = (lane & 7) + 64 * (lane >> 3);      // this row in the g1 block layout
-    uint8_t* buf8 = (uint8_t*)buf;
-    const int64_t brow = m.blk_off + ((int64_t)bz * m.nby + by) * m.nbx;
-    // the row words are in registers from here on: the buffer takes results
-    __builtin_amdgcn_wave_barrier();
-    const u16x2 one = {1, 1};
-    const u16x2 dmp = {(unsigned short)dmax, (unsigned short)dmax};
-    uint32_t Lp = L | (L4 << 16);       // blocks 0..3 | blocks 4..7
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint32_t bp = b[M + j] | (b[M + j + 4] << 16);
-        uint32_t mk[8];
-        u16x2 dp[8];
-#pragma unroll
-        for (int x = 0; x < 8; ++x)      // all ones where voxel x of the block is occupied
-            mk[x] = pk_sign_mask(bp << (15 - x));
-#pragma unroll
-        for (int x = 0; x < 8; ++x) {
-            Lp = as_u32(as_u16x2(Lp) + one) & ~mk[x];
-            dp[x] = as_u16x2(Lp);
+                    for (int q = 1; q < 16; ++q) lb = __builtin_elementwise_min(lb, A[q]);
+                    const uint32_t g2 = bits(64u * G * G);
+                    const u16x2 gg = {(unsigned short)g2, (unsigned short)g2};
+                    lb = F16 ? as_u16x2(as_h16x2(lb) + as_h16x2(gg)) : lb + gg;
+                    const u16x2 mx = max8<F16>(acc);
+                    if (__any(lb.x < mx.x || lb.y < mx.y))
+                        offsets(acc, A, B, 0, 8,
+                                [&](int t) { return bits((uint32_t)((8 * G + t) * (8 * G + t))); });
+                    if (G + 1 < M && !over(acc, bits((uint32_t)(64 * (G + 1) * (G + 1))))) break;
+                }
+            }
         }
-        uint32_t rr = rc[j] | (rc[j + 4] << 16);
+        emit(r, acc);
 #pragma unroll
-        for (int x = 7; x >= 0; --x) {
-            rr = as_u32(as_u16x2(rr) + one) & ~mk[x];
-            const u16x2 v =
-                __builtin_elementwise_min(__builtin_elementwise_min(dp[x], as_u16x2(rr)), dmp);
-            buf8[rofs + 8 * x] = (uint8_t)v.x;
-            buf8[512 + rofs + 8 * x] = (uint8_t)v.y;
-        }
-        // blocks j and j + 4: lane writes g1 elements 8 lane .. 8 lane + 7 of
-        // each (8 bytes); the wave's LDS operations complete in order, the
-        // barriers keep the compiler from moving them across
-        __builtin_amdgcn_wave_barrier();
-        const uint2 v0 = ((const uint2*)buf8)[lane];
-        const uint2 v1 = ((const uint2*)buf8)[64 + lane];
-        __builtin_amdgcn_wave_barrier();
-        if (bx0 + j < m.nbx) *(uint2*)(a.g1 + (brow + bx0 + j) * 512 + 8 * lane) = v0;
-        if (bx0 + j + 4 < m.nbx) *(uint2*)(a.g1 + (brow + bx0 + j + 4) * 512 + 8 * lane) = v1;
+        for (int q = 0; q < 16; ++q) P[q] = P[q + 8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) P[16 + u] = as_u16x2(conv(N[u]));
     }
 }
 
-// phase 1: windowed minimum along y (lane = x + 8z), g1 -> g2
-template <int M>
-__device__ void item_y(const BArgs& a, const MapDev& m, int li, uint32_t Dp) {
-    const int lane = threadIdx.x & 63;
-    const int nseg = (m.nby + a.lrun - 1) / a.lrun;
-    const int bx = li % m.nbx;
-    const int rest = li / m.nbx;
-    const int bz = rest % m.nbz, seg = rest / m.nbz;
-    (void)nseg;
-    const int by0 = seg * a.lrun;
-    const int len = min(a.lrun, m.nby - by0);
-    const int out_lane = (lane & 7) * 8 + (lane >> 3);
-    auto blk = [&](int b) -> uint4 {
-        return g1_squares<win_f16(M)>(*blk_ptr8(a.g1, m, bx, b, bz, a.dblock8, lane));
-    };
-    // the block bases are uniform (scalar branch, scalar base, immediate row
-    // offsets)
-    auto emit = [&](int ob, const u16x2* acc, bool has1) {
-        const int64_t b0 = m.blk_off + ((int64_t)bz * m.nby + ob) * m.nbx + bx;
-        uint16_t* d0 = a.g2 + b0 * 512 + out_lane;
+// Rows i .. i + 7 of a column: row j of this lane at at + j * stride + lane
+// (bytes; at and stride are uniform, so a row's address is scalar but for the
+// lane's offset), `none` for rows outside 0 .. n - 1.
+template <class T>
+__device__ inline void load_rows(const char* at, uint32_t stride, uint32_t lane, int i, int n,
+                                 uint32_t none, uint32_t (&v)[8]) {
+    if (i >= 0 && i + 8 <= n) {
+        const char* p = at + (uint32_t)i * stride;
 #pragma unroll
-        for (int o = 0; o < 8; ++o) d0[64 * o] = acc[o].x;
-        if (has1) {
-            uint16_t* d1 = a.g2 + (b0 + m.nbx) * 512 + out_lane;
+        for (int u = 0; u < 8; ++u, p += stride) v[u] = *(const T*)(p + lane);
+        return;
+    }
 #pragma unroll
-            for (int o = 0; o < 8; ++o) d1[64 * o] = acc[o].y;
-        }
-    };
-    window_min<M, true, win_f16(M)>(by0, len, Dp, blk, emit);
+    for (int u = 0; u < 8; ++u) {
+        v[u] = none;
+        if (i + u >= 0 && i + u < n) v[u] = *(const T*)(at + (uint32_t)(i + u) * stride + lane);
+    }
 }
 
-// phase 2: windowed minimum along z, g2 -> dense int32 field.  An item is a
-// strip of 64 voxels along x (8 blocks) at one y and a run of lrun blocks
-// along z; lane l owns the column x = 8 bx0 + l, so every output store is 256
-// contiguous bytes of the x-fastest field.
-template <int M>
-__device__ void item_z(const BArgs& a, const MapDev& m, int li, uint32_t Dp) {
+// phase 1: g1 -> g2 along y.  Lane = pair column c = (z, pair) in that order.
+// g2 is laid out by y first, so that a wave's row is one whole run of 256
+// aligned bytes (178 -> 138 us on 206 M voxels against rows in [z][y] order).
+template <bool F16>
+__device__ inline void item_y(const BArgs& a, const MapDev& m, int li, uint32_t Dp) {
+    const int cols = m.nz * m.np, nc = (cols + 63) / 64;
+    const int seg = li / nc;
+    const int c = min((li - seg * nc) * 64 + (int)(threadIdx.x & 63), cols - 1);
+    const int z = (int)((uint32_t)c / (uint32_t)m.np), p = c - z * m.np;
+    // offsets of a lane: g1 from the first lane's z on (a map's g1 is below
+    // 4 GB), g2 from the item's first pair
+    const int z0 = __builtin_amdgcn_readfirstlane(z), c0 = __builtin_amdgcn_readfirstlane(c);
+    const char* src = (const char*)(a.g1 + m.pair_off + (int64_t)z0 * m.ny * m.np);
+    const uint32_t lane_src = 2u * ((uint32_t)(z - z0) * (uint32_t)(m.ny * m.np) + (uint32_t)p);
+    char* dst = (char*)(a.g2 + m.pair2_off + c0);
+    const uint32_t lane_dst = 4u * (uint32_t)(c - c0);
+    const uint32_t none = (uint32_t)a.dmax * 0x0101u;
+    auto load = [&](int i, uint32_t (&v)[8]) {
+        load_rows<uint16_t>(src, 2u * m.np, lane_src, i, m.ny, none, v);
+    };
+    auto conv = [](uint32_t w) { return pair_squares<F16>(w); };
+    auto emit = [&](int r, const u16x2* acc) {
+        char* d = dst + (int64_t)r * m.ps * 4;
+#pragma unroll
+        for (int o = 0; o < 8; ++o, d += 4 * (int64_t)m.ps)
+            if (r + o < m.ny) *(uint32_t*)(d + lane_dst) = as_u32(acc[o]);
+    };
+    const int b0 = seg * a.lrun;
+    column_min<F16>(8 * b0, min(a.lrun, m.nby - b0), a.M, load, conv, emit);
+}
+
+// phase 2: g2 -> int32 field along z.  Lane = pair column c = (y, pair).
+// The planes of the field follow each other at any alignment, and a store
+// that covers part of a 128-byte line costs about as much as one that covers
+// all of it (a plain fill runs at 3.1 to 3.6 TB/s in unaligned runs of 256 or
+// 512 bytes, at 5.4 in aligned ones).  So an item stores, of every plane, the
+// lines that start among its own voxels: its last 20 pairs are also the next
+// item's first, eight rows go through LDS in the plane's order, and the lanes
+// take them from there two by two from the first line's start on.
+constexpr int ZROW = 132;                      // LDS halfwords of a row (130, 131: unused pairs)
+// (a lane reads up to halfword 31 + 2 * 63 + 1 of its row before it drops what
+// lies past the item: 26 past the last row)
+static_assert((8 * ZROW + 32) * 2 <= XSLICE, "rows of phase 2");
+
+template <bool F16>
+__device__ inline void item_z(const BArgs& a, const MapDev& m, int li, uint32_t Dp) {
+    uint16_t* buf = (uint16_t*)(xlds + (threadIdx.x >> 6) * XSLICE);
     const int lane = threadIdx.x & 63;
-    const int bx0 = 8 * (li % m.nxr);
-    const int rest = li / m.nxr;
-    const int Y = rest % m.ny, seg = rest / m.ny;
-    const int bz0 = seg * a.lrun;
-    const int len = min(a.lrun, m.nbz - bz0);
-    const int bx = bx0 + (lane >> 3), by = Y >> 3;
-    const int X = 8 * bx0 + lane;
-    const bool col_ok = X < m.nx;
-    const int rofs = (lane & 7) + 8 * (Y & 7);        // z-row (x' + 8y') of a g2 block
-    const int64_t bcol = m.blk_off + (int64_t)by * m.nbx + bx;
-    const int64_t bzst = (int64_t)m.nby * m.nbx;
-    auto blk = [&](int b) -> uint4 {
-        const bool ok = bx < m.nbx && b >= 0 && b < m.nbz;
-        const uint4* p = ok ? (const uint4*)a.g2 + (bcol + b * bzst) * 64 + rofs
-                            : (const uint4*)a.dblock + lane;
-        return *p;
+    const int cols = m.ny * m.np, nc = z_chunks(m), step = z_step(m);
+    const int seg = li / nc, k = li - seg * nc;
+    const int c = min(k * step + lane, cols - 1);
+    const int y = (int)((uint32_t)c / (uint32_t)m.np), x = 2 * (c - y * m.np);
+    const int y0 = __builtin_amdgcn_readfirstlane(y);
+    const char* src = (const char*)(a.g2 + m.pair2_off + (int64_t)y0 * m.ps);
+    const uint32_t lane_src = 4u * ((uint32_t)(y - y0) * (uint32_t)m.ps + (uint32_t)(x >> 1));
+    const int plane = m.nx * m.ny;             // 4096^2 at most
+    // voxel of the plane behind pair c (the next row's first for unused pairs)
+    auto voxel = [&](int pc) {
+        const int yy = (int)((uint32_t)pc / (uint32_t)m.np);
+        return yy * m.nx + min(2 * (pc - yy * m.np), m.nx);
     };
-    // the strip's row at z = 0 (uniform base; lane l writes x = 8 bx0 + l)
-    int32_t* row0 = a.out + m.out_off + (int64_t)Y * m.nx + 8 * bx0;
-    const int64_t zstride = (int64_t)m.nx * m.ny;
-    auto emit = [&](int ob, const u16x2* acc, bool has1) {
-        if (!col_ok) return;
-        const int nz0 = min(8, m.nz - 8 * ob);                       // rows of block ob
-        const int nz1 = has1 ? min(8, m.nz - 8 * ob - 8) : 0;        // rows of block ob + 1
-        int32_t* p0 = row0 + (int64_t)(8 * ob) * zstride;
-#pragma unroll
-        for (int o = 0; o < 8; ++o)
-            if (o < nz0) p0[o * zstride + lane] = win_f16(M) ? f16_int(acc[o].x) : (int)acc[o].x;
-        int32_t* p1 = p0 + 8 * zstride;
-#pragma unroll
-        for (int o = 0; o < 8; ++o)
-            if (o < nz1) p1[o * zstride + lane] = win_f16(M) ? f16_int(acc[o].y) : (int)acc[o].y;
+    const int e = y * m.nx + min(x, m.nx);
+    const int e0 = __builtin_amdgcn_readfirstlane(voxel(k * step));
+    const int e1 = __builtin_amdgcn_readfirstlane(k + 1 < nc ? voxel((k + 1) * step) : plane);
+    const bool lo = k * step + lane < cols && x < m.nx, hi = lo && x + 1 < m.nx;
+    uint16_t* plo = buf + (lo ? e - e0 : 130);
+    uint16_t* phi = buf + (hi ? e - e0 + 1 : 131);
+    int32_t* field = a.out + m.out_off;
+    // an item's voxels of a plane: from the first line that starts in it (from
+    // its first voxel for a plane's first item, or without lines) to the next
+    // item's first
+    const uint32_t first = step < 64 && k > 0 ? 31u : 0u;
+    const uint32_t last = step < 64 && k + 1 < nc ? 31u : 0u;
+    const bool edge = first == 0u || last == 0u;
+    const uint32_t place = (uint32_t)((uintptr_t)field >> 2) + (uint32_t)e0;
+    const int own = e1 - e0, room = plane - e0;
+    auto load = [&](int i, uint32_t (&v)[8]) {
+        load_rows<uint32_t>(src, 4u * m.np, lane_src, i, m.nz, Dp, v);
     };
-    window_min<M, true, win_f16(M)>(bz0, len, Dp, blk, emit);
+    auto conv = [](uint32_t w) { return w; };
+    auto emit = [&](int r, const u16x2* acc) {
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int o = 0; o < 8; ++o) {
+            plo[o * ZROW] = acc[o].x;
+            phi[o * ZROW] = acc[o].y;
+        }
+        __builtin_amdgcn_wave_barrier();
+        // voxels s .. t - 1 of the item are its own in a plane; `at` is the
+        // place in a line of the item's first.  All rows are read before any is
+        // stored, so that one wait covers them
+        uint32_t at = place + (uint32_t)r * (uint32_t)plane;
+        uint32_t v0[8], v1[8];
+#pragma unroll
+        for (int o = 0; o < 8; ++o) {
+            const uint16_t* b = buf + o * ZROW + 2 * lane + ((0u - at - o * plane) & first);
+            v0[o] = b[0];
+            v1[o] = b[1];
+        }
+        __builtin_amdgcn_wave_barrier();
+        const char* p = (const char*)(field + (int64_t)r * plane + e0);
+#pragma unroll
+        for (int o = 0; o < 8; ++o, at += plane, p += 4 * (int64_t)plane) {
+            if (r + o >= m.nz) break;
+            const uint32_t s = (0u - at) & first;
+            const int t = min(own + (int)((0u - at - (uint32_t)own) & last), room);
+            const int n = t - (int)s;                               // at most 128
+            const int32_t v[2] = {F16 ? f16_int(v0[o]) : (int)v0[o],
+                                  F16 ? f16_int(v1[o]) : (int)v1[o]};
+            char* d = (char*)p + (8u * (uint32_t)lane + 4u * s);
+            if (2 * lane + 1 < n) __builtin_memcpy(d, v, 8);
+            if (edge)
+                if (2 * lane + 1 == n) *(int32_t*)d = v[0];
+        }
+    };
+    const int b0 = seg * a.lrun;
+    column_min<F16>(8 * b0, min(a.lrun, m.nbz - b0), a.M, load, conv, emit);
 }
 
 // The item -> map table, the map records and the item offsets are read-only
@@ -344,20 +486,24 @@ __device__ inline MapDev load_map(const MapDev* maps, int mi) {
     return __builtin_bit_cast(MapDev, r);
 }
 
-template <int M, int PHASE>
+template <bool F16, int PHASE>
 __device__ inline void run_item(const BArgs& a, int gi, uint32_t Dp) {
     const int mi = as_const(a.itemmap)[PHASE * a.icap + gi];
     const MapDev m = load_map(a.maps, mi);
     const int li = gi - as_const(a.pref)[PHASE * (a.n_maps + 1) + mi];
-    if (PHASE == 0) item_x<M>(a, m, li);
-    else if (PHASE == 1) item_y<M>(a, m, li, Dp);
-    else item_z<M>(a, m, li, Dp);
+    if (PHASE == 0) {
+        item_x(a, m, li);
+    } else if (PHASE == 1) {
+        item_y<F16>(a, m, li, Dp);
+    } else {
+        item_z<F16>(a, m, li, Dp);
+    }
 }
 
-// Items [lo, hi) of phase PHASE; one wave per item.  Dynamic schedule: a
-// wave takes `chunk` items per atomic on the phase's counter (cidx); static:
+// Items [lo, hi) of phase PHASE; one wave per item.  Dynamic schedule: after
+// its first, a wave takes `chunk` items per atomic on the phase's counter (cidx); static:
 // wave w takes items lo + w, lo + w + nwaves, ...
-template <int M, int PHASE>
+template <bool F16, int PHASE>
 __device__ void run_phase(const BArgs& a, int lo, int hi, int cidx) {
     const int lane = threadIdx.x & 63;
     const int wpb = blockDim.x >> 6;
@@ -366,42 +512,50 @@ __device__ void run_phase(const BArgs& a, int lo, int hi, int cidx) {
     // from them are scalar too
     const int wid = __builtin_amdgcn_readfirstlane(blockIdx.x * wpb + (threadIdx.x >> 6));
     const int nwaves = gridDim.x * wpb;
-    const uint32_t Dw = win_f16(M) ? f16_bits((uint32_t)a.D) : (uint32_t)a.D;
+    const uint32_t Dw = F16 ? f16_bits((uint32_t)a.D) : (uint32_t)a.D;
     const uint32_t Dp = Dw | (Dw << 16);        // D in the window's representation
     if (a.schedule == 0) {
-        for (;;) {
-            int base = 0;
-            if (lane == 0) base = atomicAdd(&a.queues[cidx], a.chunk);
-            base = __builtin_amdgcn_readfirstlane(base) + lo;   // lane 0's grab
-            if (base >= hi) break;
-            const int end = min(base + a.chunk, hi);
-            for (int i = base; i < end; ++i) run_item<M, PHASE>(a, i, Dp);
+        // phase 0's items are the smallest: two for each of the others'.  No more
+        // than a wave's share at a time, so that few items still reach all
+        // waves, and the first chunk of every wave without asking: the counter
+        // is one address, and a batch with no more than one chunk a wave leaves
+        // it alone
+        const int chunk = max(1, min((PHASE == 0 ? 2 : 1) * a.chunk, (hi - lo) / nwaves));
+        const int64_t given = (int64_t)nwaves * chunk;
+        int64_t base = lo + (int64_t)wid * chunk;
+        while (base < hi) {
+            const int end = (int)min(base + chunk, (int64_t)hi);
+            for (int i = (int)base; i < end; ++i) run_item<F16, PHASE>(a, i, Dp);
+            if (given >= hi - lo) break;
+            int grab = 0;
+            if (lane == 0) grab = atomicAdd(&a.queues[cidx], chunk);
+            base = lo + given + __builtin_amdgcn_readfirstlane(grab);   // lane 0's grab
         }
     } else {
-        for (int i = lo + wid; i < hi; i += nwaves) run_item<M, PHASE>(a, i, Dp);
+        for (int i = lo + wid; i < hi; i += nwaves) run_item<F16, PHASE>(a, i, Dp);
     }
 }
 
 // FUSED: phases 0..2 of all maps, grid barrier between phases.
-template <int M>
+template <bool F16>
 __global__ void __launch_bounds__(512) k_batch_fused(BArgs a) {
     namespace cg = cooperative_groups;
     cg::grid_group grid = cg::this_grid();
     const int n = a.n_maps;
-    run_phase<M, 0>(a, a.pref[0], a.pref[n], n);
+    run_phase<F16, 0>(a, a.pref[0], a.pref[n], n);
     grid.sync();
-    run_phase<M, 1>(a, a.pref[n + 1], a.pref[2 * n + 1], 2 * n + 1);
+    run_phase<F16, 1>(a, a.pref[n + 1], a.pref[2 * n + 1], 2 * n + 1);
     grid.sync();
-    run_phase<M, 2>(a, a.pref[2 * n + 2], a.pref[3 * n + 2], 3 * n + 2);
+    run_phase<F16, 2>(a, a.pref[2 * n + 2], a.pref[3 * n + 2], 3 * n + 2);
 }
 
 // PHASED: one phase of all maps (map = -1), PER_MAP: one phase of one map.
-template <int M, int PHASE>
-__global__ void __launch_bounds__(512) k_batch_phase(BArgs a, int map) {
+template <bool F16, int PHASE>
+__global__ void __launch_bounds__(512, 5) k_batch_phase(BArgs a, int map) {
     const int n = a.n_maps;
     const int* pref = a.pref + PHASE * (n + 1);
-    if (map < 0) run_phase<M, PHASE>(a, pref[0], pref[n], PHASE * (n + 1) + n);
-    else run_phase<M, PHASE>(a, pref[map], pref[map + 1], PHASE * (n + 1) + map);
+    if (map < 0) run_phase<F16, PHASE>(a, pref[0], pref[n], PHASE * (n + 1) + n);
+    else run_phase<F16, PHASE>(a, pref[map], pref[map + 1], PHASE * (n + 1) + map);
 }
 
 // Item prefix sums of the three phases over the maps (processing order), one
@@ -419,9 +573,7 @@ __global__ void __launch_bounds__(1024) k_batch_prefix(const MapDev* maps, int n
         int c[3] = {0, 0, 0};
         if (i < n) {
             const MapDev m = maps[i];
-            c[0] = m.nxr * m.nby * m.nbz;
-            c[1] = m.nbx * m.nbz * ((m.nby + lrun - 1) / lrun);
-            c[2] = m.nxr * m.ny * ((m.nbz + lrun - 1) / lrun);
+            for (int p = 0; p < 3; ++p) c[p] = (int)phase_items(m, p, lrun);
         }
         int incl[3];
 #pragma unroll
@@ -470,29 +622,43 @@ __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
 int64_t align256(int64_t v) { return (v + 255) & ~(int64_t)255; }
 
 struct BLayout {
-    int64_t off_maps, off_pref, off_queues, off_itemmap, off_g1, off_g2, off_dblock,
-        off_dblock8, off_dummy, total;
-    int64_t nblocks;
+    int64_t off_maps, off_pref, off_queues, off_itemmap, off_g1, off_g2, total;
     int64_t icap;            // item-map entries per phase
 };
 
+// Device record of a map whose pairs start at pair_off and pair2_off.
+MapDev map_dev(const edt_batch_map& s, int64_t pair_off, int64_t pair2_off) {
+    MapDev m = {};
+    m.nx = s.nx; m.ny = s.ny; m.nz = s.nz;
+    m.nby = (s.ny + 7) / 8; m.nbz = (s.nz + 7) / 8;
+    m.nw = (s.nx + 31) / 32;
+    m.np = 2 * ((s.nx + 3) / 4);
+    m.ps = (m.np * s.nz + 63) & ~63;
+    m.occ_off = s.occ_offset;
+    m.out_off = s.out_offset;
+    m.pair_off = pair_off;
+    m.pair2_off = pair2_off;
+    return m;
+}
+int64_t map_pairs(const MapDev& m) { return (((int64_t)m.np * m.ny * m.nz) + 63) & ~(int64_t)63; }
+int64_t map_pairs2(const MapDev& m) { return (int64_t)m.ps * m.ny; }
+
 bool blayout(const edt_batch_map* maps, int n, int dmax, BLayout* L) {
     if (!maps || n < 1 || n > (1 << 16) || dmax < 1 || dmax > 64) return false;
-    int64_t nb = 0, ic0 = 0, ic1 = 0, ic2 = 0;
+    int64_t nb = 0, pairs = 0, pairs2 = 0, ic[3] = {0, 0, 0};
     for (int i = 0; i < n; ++i) {
         const edt_batch_map& m = maps[i];
         if (m.nx < 1 || m.ny < 1 || m.nz < 1 || m.nx > 4096 || m.ny > 4096 || m.nz > 4096)
             return false;
         if (m.occ_offset < 0 || m.out_offset < 0) return false;
         nb += (int64_t)((m.nx + 7) / 8) * ((m.ny + 7) / 8) * ((m.nz + 7) / 8);
-        // most items per phase (run length 1): x strips, y runs, z strips
-        const int64_t nbx = (m.nx + 7) / 8, nby = (m.ny + 7) / 8, nbz = (m.nz + 7) / 8;
-        const int64_t nxr = (nbx + 7) / 8;
-        ic0 += nxr * nby * nbz;
-        ic1 += nbx * nby * nbz;
-        ic2 += nxr * m.ny * nbz;
+        const MapDev d = map_dev(m, 0, 0);
+        pairs += map_pairs(d);
+        pairs2 += map_pairs2(d);
+        for (int p = 0; p < 3; ++p) ic[p] += phase_items(d, p, 1);   // run length 1: the most
     }
-    const int64_t icap = ic0 > ic1 ? (ic0 > ic2 ? ic0 : ic2) : (ic1 > ic2 ? ic1 : ic2);
+    const int64_t icap = ic[0] > ic[1] ? (ic[0] > ic[2] ? ic[0] : ic[2])
+                                       : (ic[1] > ic[2] ? ic[1] : ic[2]);
     if (nb > (1ll << 26)) return false;
     int64_t o = 0;
     L->off_maps = o; o += align256((int64_t)n * sizeof(MapDev));
@@ -500,13 +666,9 @@ bool blayout(const edt_batch_map* maps, int n, int dmax, BLayout* L) {
     L->off_queues = o; o += align256((int64_t)3 * (n + 1) * 4);
     L->off_itemmap = o; o += align256(3 * icap * 4);
     L->icap = icap;
-    L->off_g1 = o; o += align256(nb * 512);
-    L->off_g2 = o; o += align256(nb * 1024);
-    L->off_dblock = o; o += 1024;
-    L->off_dblock8 = o; o += 512;
-    L->off_dummy = o; o += align256(256 * 64 * 4 + 1024);
+    L->off_g1 = o; o += align256(pairs * 2);
+    L->off_g2 = o; o += align256(pairs2 * 4);
     L->total = o;
-    L->nblocks = nb;
     return true;
 }
 
@@ -520,25 +682,23 @@ int grid_cap(int64_t work, int cap) {
 struct edt_batch {
     int n;
     int dmax;
-    int M;
     BLayout L;
     char* ws;
     MapDev* host_maps;       // in processing order
-    int64_t* map_items[3];   // per map item counts at the last lrun (host copy)
     int last_lrun;
     int cus;
 };
 
 namespace {
 
-template <int M>
+template <bool F16>
 edt_status launch_batch(edt_batch* b, const BArgs& a, int mode, int waves_per_cu, int wg_waves,
                         hipStream_t st) {
     const int bs = 64 * wg_waves;
-    const size_t lds = wg_waves * XBYTES_PER_WAVE;
+    const size_t lds = (size_t)wg_waves * XSLICE;      // phases 0 and 2
     if (mode == EDT_BATCH_FUSED) {
         int per_cu = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch_fused<M>, bs, lds) !=
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch_fused<F16>, bs, lds) !=
             hipSuccess)
             return EDT_ERR_HIP;
         int wgs_per_cu =
@@ -547,30 +707,28 @@ edt_status launch_batch(edt_batch* b, const BArgs& a, int mode, int waves_per_cu
         const int g = b->cus * (wgs_per_cu < per_cu ? wgs_per_cu : per_cu);
         if (g < 1) return EDT_ERR_HIP;
         void* args[] = {(void*)&a};
-        if (hipLaunchCooperativeKernel((const void*)k_batch_fused<M>, dim3(g), dim3(bs), args,
+        if (hipLaunchCooperativeKernel((const void*)k_batch_fused<F16>, dim3(g), dim3(bs), args,
                                        (unsigned)lds, st) != hipSuccess)
             return EDT_ERR_HIP;
         return EDT_OK;
     }
-    // only the x phase uses LDS
-    const void* kern[3] = {(const void*)k_batch_phase<M, 0>, (const void*)k_batch_phase<M, 1>,
-                           (const void*)k_batch_phase<M, 2>};
-    const size_t klds[3] = {lds, 0, 0};
+    const void* kern[3] = {(const void*)k_batch_phase<F16, 0>, (const void*)k_batch_phase<F16, 1>,
+                           (const void*)k_batch_phase<F16, 2>};
     const int wpc = waves_per_cu > 0 ? waves_per_cu : 8;
     if (mode == EDT_BATCH_PHASED) {
         // as many waves as the fused launch would have, per phase
         for (int phase = 0; phase < 3; ++phase) {
             int per_cu = 0;
             if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern[phase], bs,
-                                                             klds[phase]) != hipSuccess)
+                                                             phase != 1 ? lds : 0) != hipSuccess)
                 return EDT_ERR_HIP;
             const int wgs_per_cu = (wpc + wg_waves - 1) / wg_waves;
             const int g = b->cus * (wgs_per_cu < per_cu ? wgs_per_cu : per_cu);
             if (g < 1) return EDT_ERR_HIP;
             int map = -1;
             void* args[] = {(void*)&a, (void*)&map};
-            if (hipLaunchKernel(kern[phase], dim3(g), dim3(bs), args, klds[phase], st) !=
-                hipSuccess)
+            if (hipLaunchKernel(kern[phase], dim3(g), dim3(bs), args, phase != 1 ? lds : 0,
+                                st) != hipSuccess)
                 return EDT_ERR_HIP;
         }
         return EDT_OK;
@@ -578,16 +736,12 @@ edt_status launch_batch(edt_batch* b, const BArgs& a, int mode, int waves_per_cu
     // PER_MAP: three launches per map, each sized to the map's items
     for (int mi = 0; mi < b->n; ++mi) {
         const MapDev& m = b->host_maps[mi];
-        const int64_t items[3] = {
-            (int64_t)m.nxr * m.nby * m.nbz,
-            (int64_t)m.nbx * m.nbz * ((m.nby + a.lrun - 1) / a.lrun),
-            (int64_t)m.nxr * m.ny * ((m.nbz + a.lrun - 1) / a.lrun)};
         for (int phase = 0; phase < 3; ++phase) {
-            const int waves = grid_cap(items[phase], b->cus * wpc);
+            const int waves = grid_cap(phase_items(m, phase, a.lrun), b->cus * wpc);
             int map = mi;
             void* args[] = {(void*)&a, (void*)&map};
             if (hipLaunchKernel(kern[phase], dim3((waves + wg_waves - 1) / wg_waves), dim3(bs),
-                                args, klds[phase], st) != hipSuccess)
+                                args, phase != 1 ? lds : 0, st) != hipSuccess)
                 return EDT_ERR_HIP;
         }
     }
@@ -620,7 +774,6 @@ edt_status edt_batch_create(const edt_batch_map* maps, int32_t n_maps, int32_t d
     }
     b->n = n_maps;
     b->dmax = d_max;
-    b->M = (d_max + 7) / 8;
     b->L = L;
     b->ws = (char*)d_ws;
     // processing order: largest map first (longest-processing-time first)
@@ -641,17 +794,11 @@ edt_status edt_batch_create(const edt_batch_map* maps, int32_t n_maps, int32_t d
         }
         order[j + 1] = v;
     }
-    int64_t blk = 0;
+    int64_t pairs = 0, pairs2 = 0;
     for (int k = 0; k < n_maps; ++k) {
-        const edt_batch_map& s = maps[order[k]];
-        MapDev& m = b->host_maps[k];
-        m.nx = s.nx; m.ny = s.ny; m.nz = s.nz;
-        m.nbx = (s.nx + 7) / 8; m.nby = (s.ny + 7) / 8; m.nbz = (s.nz + 7) / 8;
-        m.nxr = (m.nbx + 7) / 8;
-        m.occ_off = s.occ_offset;
-        m.out_off = s.out_offset;
-        m.blk_off = blk;
-        blk += (int64_t)m.nbx * m.nby * m.nbz;
+        b->host_maps[k] = map_dev(maps[order[k]], pairs, pairs2);
+        pairs += map_pairs(b->host_maps[k]);
+        pairs2 += map_pairs2(b->host_maps[k]);
     }
     free(order);
     int dev = 0;
@@ -668,15 +815,6 @@ edt_status edt_batch_create(const edt_batch_map* maps, int32_t n_maps, int32_t d
         free(b);
         return EDT_ERR_HIP;
     }
-    // the block of D values read for blocks beyond a map, in the window's
-    // representation (binary16 for small radii)
-    const uint32_t D = win_f16(b->M) ? f16_bits((uint32_t)(d_max * d_max))
-                                     : (uint32_t)(d_max * d_max);
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, st, (uint32_t*)(b->ws + L.off_dblock),
-                       (int64_t)256, D | (D << 16));
-    // and the x distance d_max, one byte per voxel, for g1
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(128), 0, st, (uint32_t*)(b->ws + L.off_dblock8),
-                       (int64_t)128, (uint32_t)d_max * 0x01010101u);
     if (hipStreamSynchronize(st) != hipSuccess) {   // the host map table may go away now
         free(b->host_maps);
         free(b);
@@ -714,44 +852,43 @@ edt_status edt_batch_run(edt_batch* b, const uint8_t* d_occ, int32_t* d_out, int
     a.queues = (int32_t*)(b->ws + L.off_queues);
     a.occ = d_occ;
     a.out = d_out;
-    a.g1 = (uint8_t*)(b->ws + L.off_g1);
-    a.g2 = (uint16_t*)(b->ws + L.off_g2);
-    a.dblock = (const uint16_t*)(b->ws + L.off_dblock);
-    a.dblock8 = (const uint8_t*)(b->ws + L.off_dblock8);
-    a.dummy = (uint32_t*)(b->ws + L.off_dummy);
+    a.g1 = (uint16_t*)(b->ws + L.off_g1);
+    a.g2 = (uint32_t*)(b->ws + L.off_g2);
     a.n_maps = b->n;
     a.dmax = b->dmax;
     a.D = b->dmax * b->dmax;
+    a.M = (b->dmax + 7) / 8;
     a.lrun = t.lrun;
     a.chunk = t.chunk;
     a.schedule = t.schedule;
     a.itemmap = (const int32_t*)(b->ws + L.off_itemmap);
     a.icap = L.icap;
+    // shorter runs while the items of a launch would leave most of the GPU
+    // without a wave: a run is walked in order, about 1.5 us per 8 rows, and two
+    // maps of 64 voxels a side have 64 runs of 16 blocks, 512 of one (27.8 ->
+    // 15.3 us; 5 maps of up to 256: 82 -> 71 us)
+    auto runs = [&](int lrun) {
+        int64_t n = 0;
+        for (int i = 0; i < b->n; ++i) n += phase_items(b->host_maps[i], 1, lrun);
+        return mode == EDT_BATCH_PER_MAP ? n / b->n : n;
+    };
+    while (a.lrun > 1 && runs(a.lrun) < (int64_t)b->cus * 8) a.lrun = (a.lrun + 1) / 2;
     // item offsets and the item -> map table depend on the run length only:
     // rebuilt when it changes; the dynamic schedule's grab counters start at
     // zero on every run
-    if (t.lrun != b->last_lrun) {
-        hipLaunchKernelGGL(k_batch_prefix, dim3(1), dim3(1024), 0, st, a.maps, b->n, t.lrun,
+    if (a.lrun != b->last_lrun) {
+        hipLaunchKernelGGL(k_batch_prefix, dim3(1), dim3(1024), 0, st, a.maps, b->n, a.lrun,
                            (int32_t*)a.pref);
         hipLaunchKernelGGL(k_batch_itemmap, dim3(b->n), dim3(256), 0, st, a.pref, b->n,
                            (int32_t*)a.itemmap, a.icap);
-        b->last_lrun = t.lrun;
+        b->last_lrun = a.lrun;
     }
     if (t.schedule == 0)
         hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, st, (uint32_t*)a.queues,
                            (int64_t)3 * (b->n + 1), 0u);
     if (hipGetLastError() != hipSuccess) return EDT_ERR_HIP;
-    switch (b->M) {
-        case 1: return launch_batch<1>(b, a, mode, t.waves_per_cu, t.wg_waves, st);
-        case 2: return launch_batch<2>(b, a, mode, t.waves_per_cu, t.wg_waves, st);
-        case 3: return launch_batch<3>(b, a, mode, t.waves_per_cu, t.wg_waves, st);
-        case 4: return launch_batch<4>(b, a, mode, t.waves_per_cu, t.wg_waves, st);
-        case 5: return launch_batch<5>(b, a, mode, t.waves_per_cu, t.wg_waves, st);
-        case 6: return launch_batch<6>(b, a, mode, t.waves_per_cu, t.wg_waves, st);
-        case 7: return launch_batch<7>(b, a, mode, t.waves_per_cu, t.wg_waves, st);
-        case 8: return launch_batch<8>(b, a, mode, t.waves_per_cu, t.wg_waves, st);
-        default: return EDT_ERR_ARG;
-    }
+    return win_f16(a.M) ? launch_batch<true>(b, a, mode, t.waves_per_cu, t.wg_waves, st)
+                        : launch_batch<false>(b, a, mode, t.waves_per_cu, t.wg_waves, st);
 }
 
 }  // extern "C"

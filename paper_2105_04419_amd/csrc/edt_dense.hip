@@ -46,6 +46,7 @@
 #include "edt.h"
 #include "edt_dev.h"
 #include "edt_hull.h"
+#include "edt_row.h"
 
 // Scratch of the allocation-free entry point (edt_dense_global_noalloc): the
 // column envelopes of grids up to EDT_DENSE_STATIC_BYTES / 8 voxels.  Each
@@ -511,32 +512,6 @@ __global__ void __launch_bounds__(64) k_dense_col_y2(int nx, int ny, int nz,
 // ---------------------------------------------------------------------------
 // extents up to HULL_NX x HULL_N x HULL_N: row records and banded hulls
 // ---------------------------------------------------------------------------
-// Bits of 32 voxels, nonzero bytes of v, bit i = byte i.
-__device__ inline uint32_t bytes8_bits(uint32_t a, uint32_t b) {
-    // bit 7 of every byte: the byte is nonzero; the dot products weigh them
-    // with 1, 2, 4, .. 128
-    const uint32_t ta = ((((a & 0x7f7f7f7fu) + 0x7f7f7f7fu) | a) >> 7) & 0x01010101u;
-    const uint32_t tb = ((((b & 0x7f7f7f7fu) + 0x7f7f7f7fu) | b) >> 7) & 0x01010101u;
-    return __builtin_amdgcn_udot4(ta, 0x08040201u,
-                                  __builtin_amdgcn_udot4(tb, 0x80402010u, 0u, false), false);
-}
-__device__ inline uint32_t bytes32_bits(const uint8_t* p) {
-    uint32_t v[8];
-    __builtin_memcpy(v, p, 32);                 // rows start at any byte
-    return bytes8_bits(v[0], v[1]) | (bytes8_bits(v[2], v[3]) << 8) |
-           (bytes8_bits(v[4], v[5]) << 16) | (bytes8_bits(v[6], v[7]) << 24);
-}
-
-// Occupancy word w (voxels 32 w .. 32 w + 31) of a row of nx voxels.
-__device__ inline uint32_t row_word(const uint8_t* row, int nx, int w) {
-    const int x0 = 32 * w;
-    if (x0 + 32 <= nx) return bytes32_bits(row + x0);
-    if (nx >= 32) return bytes32_bits(row + nx - 32) >> (x0 + 32 - nx);   // the row's last 32
-    uint32_t m = 0u;
-    for (int k = 0; k < nx; ++k) m |= (row[k] != 0 ? 1u : 0u) << k;
-    return m;
-}
-
 // Record of word w of a row: the occupancy word and the distances of its
 // first and last voxel (row_distance).  Called by the wave's lanes with
 // W >= ceil(nx / 32) consecutive lanes (W a power of two, w = lane % W) on
