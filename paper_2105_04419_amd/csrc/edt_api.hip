@@ -190,9 +190,17 @@ void launch_tile_passes(edt_ctx* c, hipStream_t st) {
     const int grid = grid_for(c->tcap * 64, 1, 16384);
     hipLaunchKernelGGL(k_pass_x_rows<M>, dim3(grid), dim3(64), 0, st, g);
     mark(c, 4, st);
-    hipLaunchKernelGGL((k_pass_win_tiles<M, 1>), dim3(grid), dim3(64), 0, st, g);
-    mark(c, 5, st);
-    hipLaunchKernelGGL((k_pass_win_tiles<M, 2>), dim3(grid), dim3(64), 0, st, g);
+    const int64_t tiles = (int64_t)((g.nbx + 7) / 8) * ((g.nby + 7) / 8) * ((g.nbz + 7) / 8);
+    if (tiles <= 64) {
+        const dim3 sgrid(grid_for(tiles * 64 * 4, 1, 8192));
+        hipLaunchKernelGGL((k_pass_win_tiles<M, 1, true>), sgrid, dim3(64), 0, st, g);
+        mark(c, 5, st);
+        hipLaunchKernelGGL((k_pass_win_tiles<M, 2, true>), sgrid, dim3(64), 0, st, g);
+    } else {
+        hipLaunchKernelGGL((k_pass_win_tiles<M, 1, false>), dim3(grid), dim3(64), 0, st, g);
+        mark(c, 5, st);
+        hipLaunchKernelGGL((k_pass_win_tiles<M, 2, false>), dim3(grid), dim3(64), 0, st, g);
+    }
     mark(c, 6, st);
 }
 
@@ -469,7 +477,7 @@ edt_status edt_global(edt_ctx* c, const edt_map* map, void* stream) {
     hipStream_t st = S(stream);
     if (map->kind == EDT_MAP_DENSE) {
         if (!map->d_occ) return EDT_ERR_ARG;
-        // one workgroup per strip of 8 blocks along x (a one-dimensional grid)
+        // strips of 8 blocks along x (a one-dimensional grid)
         if ((int64_t)((g.nbx + 7) / 8) * g.nby * g.nbz > 0x7fffffff) return EDT_ERR_ARG;
     } else if (map->kind == EDT_MAP_BLOCKS) {
         if (map->n_blocks < 0) return EDT_ERR_ARG;
@@ -484,8 +492,8 @@ edt_status edt_global(edt_ctx* c, const edt_map* map, void* stream) {
     if (map->kind == EDT_MAP_DENSE) {
         // obstacle blocks get their slots and occupancy here, the dilation
         // adds (and zeroes) the rest of the region
-        const int64_t strips = (int64_t)((g.nbx + 7) / 8) * g.nby * g.nbz;
-        hipLaunchKernelGGL(k_ingest_dense, dim3((unsigned)strips), dim3(64), 0, st, g,
+        const int64_t groups = (int64_t)((g.nbx + 7) / 8) * ((g.nby + 3) / 4) * g.nbz;
+        hipLaunchKernelGGL(k_ingest_dense, dim3((unsigned)groups), dim3(256), 0, st, g,
                            map->d_occ);
         mark(c, 1, st);
         edt_status r = dilate_region(c, st);

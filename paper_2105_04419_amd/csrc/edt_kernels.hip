@@ -23,6 +23,7 @@
 // current for every block and the marked blocks are recomputed exactly.
 #include "edt_dev.h"
 #include "edt_hull.h"
+#include "edt_row.h"
 #include "edt_win.h"
 
 namespace edt {
@@ -87,22 +88,6 @@ __device__ inline void grow_tiles(const Grid& g, bool first, int tx, int ty, int
     }
 }
 
-// Record a new tile (and its neighbourhood) and, for obstacle blocks, the
-// block in its tile's obstacle mask.  Called by a whole wave.
-__device__ inline void note_tile(const Grid& g, bool tile_created, int64_t e, bool obstacle,
-                                 int bx, int by, int bz) {
-    const int t = e >= 0 ? (int)(e >> 9) : -1;
-    const int j = wave_append(tile_created, &g.cnt[C_NTILE]);
-    if (tile_created) g.tlist[j] = t;
-    bool first = false;
-    if (obstacle && e >= 0) {
-        const int local = (int)(e & 511);
-        atomicOr(&g.tobst[(int64_t)t * 16 + (local >> 5)], 1u << (local & 31));
-        first = atomicOr(&g.tflag[t], 1) == 0;
-    }
-    grow_tiles(g, first, bx >> 3, by >> 3, bz >> 3);
-}
-
 // Pool slots for the lanes that just created a block at tile entry e: one
 // counter atomic per wave.  Returns the slot, or -1 (not created / pool full).
 __device__ inline int32_t claim_slots(const Grid& g, bool created, int64_t e,
@@ -136,64 +121,81 @@ __device__ inline void block_of(int nxb, int nyb, int& bx, int& by, int& bz) {
 
 // Dense grid.  One wave per strip of 8 blocks along x; lane = row (y + 8z).
 // Each lane reads 64 contiguous bytes of its row, packs 8 bits per block and
-// the wave ballot decides whether a block holds any obstacle.
-__global__ void __launch_bounds__(64) k_ingest_dense(Grid g, const uint8_t* __restrict__ occ) {
-    const int lane = threadIdx.x;
-    int sx, by, bz;
-    block_of((g.nbx + 7) / 8, g.nby, sx, by, bz);
+// the wave ballot decides whether a block holds any obstacle.  A workgroup
+// takes four strips next to each other along y: they lie in one tile, where
+// their 32 blocks are one word of the obstacle mask, and no other workgroup
+// holds them; so it finds or creates the tile once, stores the word, and takes
+// the slots with one atomic.  (One atomic per lane and address kept 600 strips
+// of 203 x 117 x 75 waiting: 24 us, now 8.)
+__global__ void __launch_bounds__(256) k_ingest_dense(Grid g, const uint8_t* __restrict__ occ) {
+    __shared__ uint32_t word;                 // blocks holding an obstacle, byte = strip
+    __shared__ int32_t tile, first_slot;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int sx, byq, bz;
+    block_of((g.nbx + 7) / 8, (g.nby + 3) / 4, sx, byq, bz);
+    const int by = 4 * byq + w;
     const int bx0 = sx * 8;
+    if (threadIdx.x == 0) word = 0u;
+    __syncthreads();
     const int y = 8 * by + (lane & 7), z = 8 * bz + (lane >> 3);
     const int x0 = 8 * bx0;
     uint32_t bytes[8];
     const bool row_ok = (y < g.ny) && (z < g.nz);
     const uint8_t* row = occ + ((int64_t)z * g.ny + y) * (int64_t)g.nx;
-    if (row_ok && x0 + 64 <= g.nx && (((uintptr_t)(row + x0)) & 15) == 0) {
-        const uint4* p = (const uint4*)(row + x0);
+    // 64 voxels in two words (16-byte loads at any alignment)
+    uint32_t w0 = 0u, w1 = 0u;
+    if (row_ok) {
+        w0 = row_word(row, g.nx, 2 * sx);
+        if (x0 + 32 < g.nx) w1 = row_word(row, g.nx, 2 * sx + 1);
+    }
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            uint4 v = p[w];
-            uint32_t a[4] = {v.x, v.y, v.z, v.w};
+    for (int j = 0; j < 8; ++j) bytes[j] = ((j < 4 ? w0 : w1) >> (8 * (j & 3))) & 0xffu;
+    // bit j: block bx0 + j holds an obstacle
+    uint32_t m8 = 0u;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint32_t lo = a[2 * h], hi = a[2 * h + 1];
-                uint32_t b = 0;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    b |= (((lo >> (8 * k)) & 0xff) != 0) << k;
-                    b |= (((hi >> (8 * k)) & 0xff) != 0) << (k + 4);
-                }
-                bytes[2 * w + h] = b;
+    for (int j = 0; j < 8; ++j)
+        if (__ballot(bytes[j] != 0) != 0 && bx0 + j < g.nbx) m8 |= 1u << j;
+    if (lane == 0 && m8) atomicOr(&word, m8 << (8 * w));
+    __syncthreads();
+    const uint32_t all = word;
+    if (all == 0u) return;
+    if (w == 0) {
+        bool first = false;
+        if (lane == 0) {
+            static_assert(C_NDIL == C_NBLK + 1 && C_NBLK == 0, "adjacent counters");
+            bool tnew = false;
+            const int32_t t = hinsert(g.tkeys, g.tmask, pack_key(sx, by >> 3, bz >> 3), &tnew);
+            tile = t;
+            if (t < 0) {
+                set_error(g, -3 /* EDT_ERR_CAPACITY */);
+            } else {
+                const unsigned long long nb = (unsigned long long)__popc(all);
+                first_slot = (int32_t)(uint32_t)atomicAdd((unsigned long long*)&g.cnt[C_NBLK],
+                                                          nb | (nb << 32));
+                g.tobst[(int64_t)t * 16 + (((by & 7) + 8 * (bz & 7)) >> 2)] = all;
+                first = atomicOr(&g.tflag[t], 1) == 0;
+                if (tnew) g.tlist[atomicAdd(&g.cnt[C_NTILE], 1)] = t;
             }
         }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            uint32_t b = 0;
-            for (int k = 0; k < 8; ++k) {
-                int x = x0 + 8 * j + k;
-                if (row_ok && x < g.nx && row[x]) b |= 1u << k;
-            }
-            bytes[j] = b;
+        grow_tiles(g, first, sx, by >> 3, bz >> 3);
+    }
+    __syncthreads();
+    const int32_t t = tile;
+    const int base = first_slot + __popc(all & ((1u << (8 * w)) - 1u));
+    // lane j < 8: the slot of block bx0 + j (-1: none, or the pool is full)
+    int32_t slot = -1;
+    if (lane < 8 && ((m8 >> lane) & 1u) && t >= 0) {
+        const int idx = base + __popc(m8 & ((1u << lane) - 1u));
+        if (idx < g.max_blocks) {
+            slot = idx;
+            g.bkey[slot] = pack_key(bx0 + lane, by, bz);
+            g.flags[slot] = F_DILATED;
+            g.tslots[(int64_t)t * 512 + block_local(lane, by, bz)] = slot;
+        } else {
+            set_error(g, -3 /* EDT_ERR_CAPACITY */);
+            g.cnt[C_ABORT] = 1;
         }
     }
-    // lane j (< 8) learns whether block bx0 + j holds an obstacle
-    bool mine = false;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const bool any = __ballot(bytes[j] != 0) != 0;
-        if (lane == j) mine = any && (bx0 + j < g.nbx);
-    }
-    int64_t e = -1;
-    bool created = false, tnew = false;
-    const unsigned long long key = pack_key(bx0 + lane, by, bz);
-    if (mine) {
-        e = insert_block(g, bx0 + lane, by, bz, &created, &tnew);
-        if (e < 0) set_error(g, -3);
-    }
-    note_tile(g, tnew, e, mine, bx0 + lane, by, bz);
-    const int32_t slot = claim_slots(g, created, e, key, F_DILATED);
-    const int ndil = __popcll(__ballot(slot >= 0));
-    if (lane == 0 && ndil) atomicAdd(&g.cnt[C_NDIL], ndil);
     uint8_t* occ8 = (uint8_t*)g.occ;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -1239,7 +1241,12 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 // the pass axis inside a tile (64 columns per tile), with M blocks of context
 // on each side taken from the neighbouring tiles.  Absent blocks hold no
 // obstacle within d_max, so they read as the constant D block.
-template <int M, int AXIS>
+// SPLIT (extents of at most 64 tiles, where whole columns are too few waves
+// for the GPU's 1,024 SIMDs): a column goes to four or two waves, of two or
+// four blocks each, that repeat its context (pass Y of one tile at d_max 20 7.5
+// -> 5.0 us in four, 6.0 in two; of 16 tiles at d_max 50 24 -> 18 us in two,
+// while pass Z takes 10 us in two and 13 in four).
+template <int M, int AXIS, bool SPLIT>
 __global__ void __launch_bounds__(64) k_pass_win_tiles(Grid g) {
     constexpr int NB = 8 + 2 * M;
     __shared__ int32_t sl[NB];
@@ -1249,7 +1256,11 @@ __global__ void __launch_bounds__(64) k_pass_win_tiles(Grid g) {
     constexpr bool F16 = win_f16(M);
     const uint32_t Dw = F16 ? f16_bits((uint32_t)g.D) : (uint32_t)g.D;
     const uint32_t Dpw = Dw | (Dw << 16);     // D in the window's representation
-    for (int64_t it = blockIdx.x; it < ncol; it += gridDim.x) {
+    const int sp = !SPLIT ? 0 : ncol <= 512 ? 2 : ncol <= 4096 ? 1 : 0;
+    const int count = 8 >> sp;                // output blocks of a wave
+    for (int64_t iw = blockIdx.x; iw < ncol << sp; iw += gridDim.x) {
+        const int64_t it = iw >> sp;
+        const int j0 = SPLIT ? (int)(iw & ((1 << sp) - 1)) * count : 0;
         const int32_t* ti = g.tinfo + (it >> 6) * 8;
         const int ca = (int)(it & 7), cb = (int)((it >> 3) & 7);
         // the lookups and the window's first loads form a chain of
@@ -1263,7 +1274,8 @@ __global__ void __launch_bounds__(64) k_pass_win_tiles(Grid g) {
         __syncthreads();
         bool any = false;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) any = any || sl[M + j] >= 0;
+        for (int j = 0; j < 8; ++j)
+            any = any || (sl[M + j] >= 0 && (!SPLIT || (j >= j0 && j < j0 + count)));
         if (any) {
             // skip masks over window positions j (block j - M): least input
             // of the block, D for absent blocks and past the context
@@ -1273,14 +1285,17 @@ __global__ void __launch_bounds__(64) k_pass_win_tiles(Grid g) {
                 const int32_t s2 = sl[lane];
                 if (s2 >= 0) bm = bmin[s2];
             }
+            // (bit 0 is the first block of the wave's own window, block j0 - M)
             WinSkip sk;
-            sk.d = __ballot(bm >= g.D);
+            const uint64_t flat = __ballot(bm >= g.D);
+            sk.d = flat >> j0;
 #pragma unroll
             for (int G = 0; G < M; ++G) {
                 const int kg = G == 0 ? 1 : 8 * G;
-                sk.g[G] = __ballot(bm + kg * kg >= g.D);
+                sk.g[G] = __ballot(bm + kg * kg >= g.D) >> j0;
             }
-            if (sk.d == ~0ull) {
+            const uint64_t window = SPLIT ? (1ull << (count + 2 * M)) - 1ull : ~0ull;
+            if ((sk.d & window) == window) {
                 // every block of the window is D everywhere, so is every
                 // output: pass Y records the block minimum D and stores no
                 // g2 (its readers take the shared D block); pass Z stores s
@@ -1288,6 +1303,7 @@ __global__ void __launch_bounds__(64) k_pass_win_tiles(Grid g) {
                 // every store of s), and the maximum D
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
+                    if (SPLIT && (j < j0 || j >= j0 + count)) continue;
                     const int32_t slot = __builtin_amdgcn_readfirstlane(sl[M + j]);
                     if (slot < 0) continue;
                     if (AXIS == 1) {
@@ -1305,7 +1321,7 @@ __global__ void __launch_bounds__(64) k_pass_win_tiles(Grid g) {
             // resident) instead of its own copy
             auto blk = [&](int b) -> uint4 {
                 const int j = b + M;
-                const int32_t s2 = (j < NB && !((sk.d >> j) & 1ull)) ? sl[j] : -1;
+                const int32_t s2 = (j < NB && !((flat >> j) & 1ull)) ? sl[j] : -1;
                 const uint4* p = s2 >= 0 ? (const uint4*)src + (int64_t)s2 * 64 + lane
                                          : (const uint4*)g.dblock + lane;
                 return *p;
@@ -1316,7 +1332,7 @@ __global__ void __launch_bounds__(64) k_pass_win_tiles(Grid g) {
                 win_store<AXIS, F16>(g, slot0, slot1, acc, lane);
             };
             auto need = [&](int ob) { return sl[M + ob] >= 0 || sl[M + ob + 1] >= 0; };
-            window_min<M, false, F16>(0, 8, Dpw, blk, emit, need, sk);
+            window_min<M, false, F16>(j0, SPLIT ? count : 8, Dpw, blk, emit, need, sk);
         }
         __syncthreads();
     }
