@@ -30,13 +30,8 @@ struct edt_ctx {
     int64_t ucap;       // update hash capacity
     int64_t stats_host[C_N];
     bool interior_valid;   // edt_interior ran after the last global / update
-    int32_t* scan_xyz;     // change list built by edt_integrate_scan
-    uint8_t* scan_state;
-    int32_t* scan_cnt;     // [0] free entries, [1] hit entries, [2] list length,
-                           // [3] finished workgroups of the hit kernel, [4..5] int64
-                           // number of visited-voxel slots
-    int64_t* scan_off;     // per ray: first slot within its group of 1024 rays
-    int64_t* scan_blk;     // per group of 1024 rays: slot total, then first slot
+    int32_t* scan_xyz;     // voxels that edt_integrate_scan sets free
+    int32_t* scan_cnt;     // its length (zero between calls)
 };
 
 namespace {
@@ -56,7 +51,7 @@ struct Layout {
 enum {
     O_TKEYS, O_TSLOTS, O_BKEY, O_OCC, O_G1, O_G2, O_S, O_BMAX, O_FLAGS, O_CNT,
     O_YI, O_ZI, O_SEED, O_DIRTY, O_XS, O_YS, O_NEWDIL, O_CHGA, O_CHGR,
-    O_UKEYS, O_UVALS, O_UPOS, O_DBLOCK, O_TOBST, O_TLIST, O_BMIN, O_TINFO, O_TFLAG, O_IIDX, O_ILIST, O_IC1, O_IC2, O_SCANXYZ, O_SCANST, O_SCANCNT, O_SCANOFF, O_SCANBLK, O_N
+    O_UKEYS, O_UVALS, O_UPOS, O_DBLOCK, O_TOBST, O_TLIST, O_BMIN, O_TINFO, O_TFLAG, O_IIDX, O_ILIST, O_IC1, O_IC2, O_SCANXYZ, O_SCANCNT, O_N
 };
 
 bool valid_cfg(const edt_config* c) {
@@ -94,7 +89,7 @@ bool layout_of(const edt_config* c, Layout* L) {
         mb * 4, mb * 4, mb * 4, mb * 4, mb * 4, mb * 4, mb * 4, mb * 64, mb * 64,
         L->ucap * 8, L->ucap * 4, mc * 4, 1024,
         L->tcap * 64, L->tcap * 4, mb * 4, L->tcap * 32, L->tcap * 4,
-        mi ? mb * 4 : 0, mi * 4, mi * 1024, mi * 1024, mc * 12, mc, 256, mc * 8, (mc / 1024 + 1) * 16};
+        mi ? mb * 4 : 0, mi * 4, mi * 1024, mi * 1024, mc * 12, 256};
     int64_t o = 0;
     for (int i = 0; i < O_N; ++i) {
         L->off[i] = o;
@@ -307,10 +302,7 @@ static void bind_workspace(edt_ctx* c, const edt_config* cfg, const Layout& L, c
     g.ic1 = (uint16_t*)(b + L.off[O_IC1]);
     g.ic2 = (uint16_t*)(b + L.off[O_IC2]);
     c->scan_xyz = (int32_t*)(b + L.off[O_SCANXYZ]);
-    c->scan_state = (uint8_t*)(b + L.off[O_SCANST]);
     c->scan_cnt = (int32_t*)(b + L.off[O_SCANCNT]);
-    c->scan_off = (int64_t*)(b + L.off[O_SCANOFF]);
-    c->scan_blk = (int64_t*)(b + L.off[O_SCANBLK]);
 }
 
 // Enqueues the initial state of a freshly bound workspace: empty tile and
@@ -324,6 +316,7 @@ static edt_status init_workspace(edt_ctx* c, const Layout& L, hipStream_t st) {
     hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(L.ucap, 256, 4096)), dim3(256), 0, st, g.uvals,
                        L.ucap, -1);
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, g.cnt, (int64_t)64, 0);
+    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, c->scan_cnt, (int64_t)1, 0);
     // the block of D values that the window passes read for absent blocks of
     // g1 / g2, in their representation (binary16 for small radii)
     const uint32_t dw = win_f16(g.R) ? f16_bits((uint32_t)g.D) : (uint32_t)g.D;
@@ -580,24 +573,22 @@ edt_status edt_grow(edt_ctx* c, int64_t max_blocks, void* d_ws, int64_t ws_bytes
     return EDT_OK;
 }
 
-// The incremental transform over n change entries; n_dev, when given, holds
-// the entry count on the device and n is then only its upper bound (grids).
-static edt_status run_update(edt_ctx* c, const int32_t* d_xyz, const uint8_t* d_state,
-                             int64_t n, const int32_t* n_dev, hipStream_t st) {
+// The incremental transform over the entries of ch.
+static edt_status run_update(edt_ctx* c, const Changes& ch, hipStream_t st) {
     c->interior_valid = false;
     Grid& g = c->g;
     const int mb = g.max_blocks;
-    // every update kernel loops grid-stride; a device-side count only bounds
-    // n, so its grids stay moderate
-    const int tn = grid_for(n_dev && n > 65536 ? 65536 : n, 256, 4096);
+    // every update kernel loops grid-stride; the list of a scan is only
+    // bounded here, so its share of the grids stays moderate
+    const int64_t n = ch.n + ch.nray;
+    const int tn = grid_for(ch.nfree && n > 65536 ? 65536 : n, 256, 4096);
     const int w3 = (2 * g.R + 1) * (2 * g.R + 1) * (2 * g.R + 1);
     // dedupe, and every block the call needs exists before any occupancy
     // changes
-    hipLaunchKernelGGL(k_upd_dedupe_alloc, dim3(tn), dim3(256), 0, st, g, d_xyz, d_state, n, n_dev);
+    hipLaunchKernelGGL(k_upd_dedupe_alloc, dim3(tn), dim3(256), 0, st, g, ch);
     // occupancy changes and the dilation of the listed blocks in one launch
     const int td = grid_for((int64_t)n * w3, 256, 4096);
-    hipLaunchKernelGGL(k_upd_apply_dilate, dim3(tn + td), dim3(256), 0, st, g, d_xyz, d_state, n,
-                       n_dev, tn);
+    hipLaunchKernelGGL(k_upd_apply_dilate, dim3(tn + td), dim3(256), 0, st, g, ch, tn);
     // fronts: one workgroup per seed block (at most one per change entry),
     // wide enough for the seed's whole neighbourhood when it has at most 1024
     // blocks
@@ -609,7 +600,7 @@ static edt_status run_update(edt_ctx* c, const int32_t* d_xyz, const uint8_t* d_
     gu.lrun = 2;
     const int nxw = grid_for(mb, 1, 2048);
     hipLaunchKernelGGL(k_upd_x_items, dim3(nxw + grid_for(2 * (int64_t)mb + 64, 64, 2048)), dim3(64),
-                       0, st, gu, nxw);
+                       0, st, gu, nxw, ch.nfree);
     launch_pass(c, gu, 1, st, g.list_yi, (int)C_NYI, (uint32_t)F_YS);
     launch_pass(c, gu, 2, st, g.list_zi, (int)C_NZI, (uint32_t)F_DIRTY);
     LAUNCH_CHECK();
@@ -622,7 +613,8 @@ edt_status edt_update(edt_ctx* c, const int32_t* d_xyz, const uint8_t* d_state, 
     if (n == 0) return EDT_OK;
     if (!d_xyz || !d_state) return EDT_ERR_ARG;
     if (n > c->g.max_changes) return EDT_ERR_CAPACITY;
-    return run_update(c, d_xyz, d_state, n, nullptr, S(stream));
+    const Changes ch = {d_xyz, d_state, n, nullptr, nullptr, nullptr, nullptr, 0};
+    return run_update(c, ch, S(stream));
 }
 
 edt_status edt_integrate_scan(edt_ctx* c, const int32_t* d_origin, const int32_t* d_ends,
@@ -634,24 +626,18 @@ edt_status edt_integrate_scan(edt_ctx* c, const int32_t* d_origin, const int32_t
     const int64_t mc = g.max_changes;
     if (n > mc) return EDT_ERR_CAPACITY;
     hipStream_t st = S(stream);
-    // list: free entries first (capacity mc - n), then one entry per hit
-    const int64_t cap = mc - n;
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, c->scan_cnt, (int64_t)4, 0);
-    int64_t* total = (int64_t*)(c->scan_cnt + 4);
-    const int64_t nb = (n + 1023) / 1024;
-    int64_t* btot = c->scan_blk;
-    int64_t* bpre = c->scan_blk + nb;
-    hipLaunchKernelGGL(k_scan_offsets, dim3((unsigned)nb), dim3(1024), 0, st, g, d_origin, d_ends,
-                       n, c->scan_off, btot);
-    hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(1024), 0, st, (const int64_t*)btot, nb, bpre,
-                       total);
-    hipLaunchKernelGGL(k_scan_clear, dim3(2048), dim3(1024), 0, st, g, d_origin, d_ends, d_hits, n,
-                       (const int64_t*)c->scan_off, (const int64_t*)bpre, (const int64_t*)total,
-                       c->scan_cnt, c->scan_xyz, c->scan_state, cap);
-    hipLaunchKernelGGL(k_scan_hits, dim3(grid_for(n, 256, 1024)), dim3(256), 0, st, g, d_origin,
-                       d_ends, d_hits, n, c->scan_cnt, c->scan_xyz, c->scan_state, cap);
+    // at most max_changes entries: one per ray, the free voxels in the rest
+    const Changes ch = {c->scan_xyz, nullptr, mc - n, c->scan_cnt, d_origin, d_ends, d_hits, n};
+    // a group of rays is split over workgroups when the groups alone leave
+    // the chip idle, at most to one chunk of its block entries each
+    const int64_t groups = (n + SCAN_RAYS - 1) / SCAN_RAYS;
+    const int64_t most = SCAN_RAYS * (int64_t)(g.nbx + g.nby + g.nbz);
+    int64_t split = 1024 / groups < 1 ? 1 : 1024 / groups;
+    if (split > (most + SCAN_T - 1) / SCAN_T) split = (most + SCAN_T - 1) / SCAN_T;
+    hipLaunchKernelGGL(k_scan_clear, dim3(grid_for(groups, 1, 65536), (unsigned)split), dim3(SCAN_T),
+                       0, st, g, ch, c->scan_xyz);
     LAUNCH_CHECK();
-    return run_update(c, c->scan_xyz, c->scan_state, mc, c->scan_cnt + 2, st);
+    return run_update(c, ch, st);
 }
 
 edt_status edt_query(edt_ctx* c, const int32_t* d_xyz, int64_t n, int32_t* d_out, void* stream) {

@@ -918,10 +918,14 @@ __device__ inline void pass_x_body(const Grid& g, const int32_t* list, int list_
 // Incremental transform: pass x over the xs list and the y / z work items
 // are independent, so they share one launch; the first nxw workgroups take
 // pass x.
-__global__ void __launch_bounds__(64) k_upd_x_items(Grid g, int nxw) {
+__global__ void __launch_bounds__(64) k_upd_x_items(Grid g, int nxw, int32_t* nfree) {
     __shared__ int32_t nb[72];
-    // no kernel from here on reads the cancel mark: clear it for the next call
-    if (blockIdx.x == 0 && threadIdx.x == 0) g.cnt[C_UABORT] = 0;
+    // no kernel from here on reads the cancel mark or the scan's list length:
+    // clear them for the next call
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        g.cnt[C_UABORT] = 0;
+        if (nfree) *nfree = 0;
+    }
     if ((int)blockIdx.x < nxw) pass_x_body(g, g.list_xs, C_NXS, blockIdx.x, nxw, nb);
     else items_update_body(g, (int64_t)blockIdx.x - nxw, (int64_t)gridDim.x - nxw);
 }
@@ -1532,6 +1536,41 @@ __global__ void k_query(Grid g, const int32_t* __restrict__ xyz, int64_t n, int3
 // incremental update
 // ---------------------------------------------------------------------------
 
+// The change entries of an update: n explicit ones (voxel, new state), or,
+// with `nfree` set, those of a range scan: the first min(*nfree, n) entries of
+// the list set a voxel free, and entry min(*nfree, n) + r is ray r of the
+// scan, which sets its end voxel occupied if the ray has a return and both
+// its ends lie in the extent (the last entry of a voxel counts, so hits win).
+struct Changes {
+    const int32_t* xyz;
+    const uint8_t* state;
+    int64_t n;
+    int32_t* nfree;
+    const int32_t* origin;
+    const int32_t* ends;
+    const uint8_t* hits;
+    int64_t nray;
+};
+
+__device__ inline bool in_extent(const Grid& g, const int v[3]) {
+    return v[0] >= 0 && v[1] >= 0 && v[2] >= 0 && v[0] < g.nx && v[1] < g.ny && v[2] < g.nz;
+}
+
+__device__ inline int64_t list_entries(const Changes& c) {
+    if (!c.nfree) return c.n;
+    const int64_t f = *c.nfree;
+    return f < c.n ? f : c.n;
+}
+
+// Voxel of entry i (nl: list_entries); returns its new state.
+__device__ inline bool change_voxel(const Changes& c, int64_t i, int64_t nl, int v[3]) {
+    const int32_t* p = i < nl ? c.xyz + 3 * i : c.ends + 3 * (i - nl);
+    v[0] = p[0];
+    v[1] = p[1];
+    v[2] = p[2];
+    return i < nl ? !c.nfree && c.state[i] != 0 : true;
+}
+
 __device__ inline bool upd_winner(const Grid& g, int64_t i) {
     const int32_t h = g.upos[i];
     return h >= 0 && g.uvals[h] == (int32_t)i;
@@ -1579,10 +1618,13 @@ __device__ inline void init_slots(const Grid& g, int32_t slot) {
 // dilation list's (zeroed by the previous call's fronts kernel), to which
 // every workgroup of this kernel appends.  A cancelled update sets
 // C_UABORT, which the x-items kernel clears after its last reader.
-__global__ void k_upd_dedupe_alloc(Grid g, const int32_t* __restrict__ xyz,
-                                   const uint8_t* __restrict__ state, int64_t n0,
-                                   const int32_t* n_dev) {
-    const int64_t n = n_dev ? (int64_t)*n_dev : n0;
+__global__ void k_upd_dedupe_alloc(Grid g, Changes c) {
+    const int64_t nl = list_entries(c), n = nl + c.nray;
+    bool o_in = true;
+    if (c.nray) {
+        const int o[3] = {c.origin[0], c.origin[1], c.origin[2]};
+        o_in = in_extent(g, o);
+    }
     if (blockIdx.x == 0 && threadIdx.x >= C_NYI && threadIdx.x < C_N &&
         threadIdx.x != C_NNEWDIL)
         g.cnt[threadIdx.x] = 0;
@@ -1592,26 +1634,30 @@ __global__ void k_upd_dedupe_alloc(Grid g, const int32_t* __restrict__ xyz,
         bool want = false;
         int bx = 0, by = 0, bz = 0;
         if (i < n) {
-            const int x = xyz[3 * i], y = xyz[3 * i + 1], z = xyz[3 * i + 2];
-            g.upos[i] = -1;
-            if (x < 0 || y < 0 || z < 0 || x >= g.nx || y >= g.ny || z >= g.nz) {
+            int v[3];
+            const bool st = change_voxel(c, i, nl, v);
+            const bool inside = in_extent(g, v);
+            int32_t h = -1;
+            if (i >= nl && !(c.hits[i - nl] && o_in && inside)) {
+                // a ray that sets no voxel
+            } else if (!inside) {
                 set_error(g, -2);
                 g.cnt[C_UABORT] = 1;
             } else {
-                const unsigned long long key = (unsigned long long)x +
-                    (unsigned long long)g.nx * ((unsigned long long)y + (unsigned long long)g.ny * z);
+                const unsigned long long key = (unsigned long long)v[0] +
+                    (unsigned long long)g.nx * ((unsigned long long)v[1] + (unsigned long long)g.ny * v[2]);
                 bool created;
-                const int32_t h = hinsert(g.ukeys, g.umask, key, &created);
+                h = hinsert(g.ukeys, g.umask, key, &created);
                 if (h < 0) {
                     set_error(g, -3);
                     g.cnt[C_UABORT] = 1;
                 } else {
-                    g.upos[i] = h;
                     atomicMax(&g.uvals[h], (int32_t)i);
-                    want = state[i] != 0;
-                    bx = x >> 3; by = y >> 3; bz = z >> 3;
+                    want = st;
+                    bx = v[0] >> 3; by = v[1] >> 3; bz = v[2] >> 3;
                 }
             }
+            g.upos[i] = h;
         }
         bool created = false;
         int64_t e = -1;
@@ -1649,9 +1695,8 @@ __global__ void k_upd_dedupe_alloc(Grid g, const int32_t* __restrict__ xyz,
 // clears its entry once it has read it (the entries that lose to it only
 // ever compare the stored index with their own), and a call cancelled before
 // this kernel clears the entry of every input.  Workgroups vb of vgrid.
-__device__ inline void upd_apply_body(const Grid& g, const int32_t* __restrict__ xyz,
-                                      const uint8_t* __restrict__ state, int64_t n,
-                                      int64_t vb, int64_t vgrid) {
+__device__ inline void upd_apply_body(const Grid& g, const Changes& c, int64_t vb, int64_t vgrid) {
+    const int64_t nl = list_entries(c), n = nl + c.nray;
     const int64_t t0 = vb * blockDim.x + threadIdx.x, stride = vgrid * blockDim.x;
     {
         // the blocks listed for dilation are being dilated by the other
@@ -1677,14 +1722,14 @@ __device__ inline void upd_apply_body(const Grid& g, const int32_t* __restrict__
             const int32_t h = g.upos[i];
             g.ukeys[h] = KEY_EMPTY;
             g.uvals[h] = -1;
-            const int x = xyz[3 * i], y = xyz[3 * i + 1], z = xyz[3 * i + 2];
-            slot = find_block(g, x >> 3, y >> 3, z >> 3);
+            int p[3];
+            const bool tgt = change_voxel(c, i, nl, p);
+            slot = find_block(g, p[0] >> 3, p[1] >> 3, p[2] >> 3);
             if (slot >= 0) {
-                const int v = (x & 7) + 8 * (y & 7) + 64 * (z & 7);
+                const int v = (p[0] & 7) + 8 * (p[1] & 7) + 64 * (p[2] & 7);
                 const uint32_t bit = 1u << (v & 31);
                 const int64_t w = (int64_t)slot * 16 + (v >> 5);
                 const bool cur = (g.occ[w] & bit) != 0;
-                const bool tgt = state[i] != 0;
                 if (tgt != cur) {
                     if (tgt) {
                         atomicOr(&g.occ[w], bit);
@@ -1757,11 +1802,8 @@ __device__ inline void upd_dilate_body(const Grid& g, int64_t vb, int64_t vgrid)
 // bits may have changed: the fronts kernel then restores them from the
 // change masks (and undoes the call's F_DILATED marks), so a cancelled call
 // still leaves the map as it was.
-__global__ void k_upd_apply_dilate(Grid g, const int32_t* __restrict__ xyz,
-                                   const uint8_t* __restrict__ state, int64_t n0,
-                                   const int32_t* n_dev, int napply) {
-    const int64_t n = n_dev ? (int64_t)*n_dev : n0;
-    if ((int)blockIdx.x < napply) upd_apply_body(g, xyz, state, n, blockIdx.x, napply);
+__global__ void k_upd_apply_dilate(Grid g, Changes c, int napply) {
+    if ((int)blockIdx.x < napply) upd_apply_body(g, c, blockIdx.x, napply);
     else upd_dilate_body(g, (int64_t)blockIdx.x - napply, (int64_t)gridDim.x - napply);
 }
 
@@ -1971,280 +2013,200 @@ __global__ void __launch_bounds__(1024) k_upd_fronts(Grid g) {
 // end voxel of a ray with a return becomes occupied, and hits win.
 // ---------------------------------------------------------------------------
 
-// Voxel entered at crossing j of the ray (crossings numbered per axis: the
-// |dx| crossings on x first, then y, then z).  On every axis b the voxel has
-// moved by the number of b-crossings up to it: all strictly earlier ones, and
-// those at the same parameter when b comes before the crossing's axis (its
-// own axis counts the crossing itself).
-__device__ inline void ray_crossing_voxel(const int o[3], const int d[3], const int ad[3],
-                                          int64_t j, int v[3]) {
-    int a = 0;
-    while (a < 2 && j >= ad[a]) { j -= ad[a]; ++a; }
+// Voxel entered at crossing j of axis a of the ray.  On every other axis b the
+// voxel has moved by the number of b-crossings up to it: crossing i' of axis b
+// is strictly earlier iff (2i' + 1) |d_a| < (2j + 1) |d_b|, and one at the
+// same parameter counts when b comes before a.  The products stay below 2^42,
+// exact in binary64, and the quotients below 2^21, so the product with the
+// reciprocal in binary32 is off by less than a half and one step up or down
+// makes the floor exact.
+__device__ inline void ray_crossing_voxel(const int o[3], const int d[3], const int ad[3], int a,
+                                          int j, int v[3]) {
+    const int Q = a == 0 ? ad[0] : a == 1 ? ad[1] : ad[2];
+    const double q = (double)Q, rq = (double)__builtin_amdgcn_rcpf((float)Q);
+    int c[3];
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
-        int64_t c;
-        if (b == a) {
-            c = j + 1;
-        } else if (ad[b] == 0) {
-            c = 0;
-        } else {
-            // crossing i' of axis b is earlier iff (2i' + 1) |d_a| < (2j + 1) |d_b|
-            const int64_t P = (2 * j + 1) * (int64_t)ad[b], Q = ad[a];
-            // floor(P / Q) and ceil(P / Q), in 32 bits when P fits
-            int64_t fl, ce;
-            if (P < (1ll << 31)) {
-                const uint32_t p32 = (uint32_t)P, q32 = (uint32_t)Q;
-                const uint32_t f = p32 / q32;
-                fl = f;
-                ce = f + (f * q32 != p32 ? 1 : 0);
-            } else {
-                fl = P / Q;
-                ce = fl + (fl * Q != P ? 1 : 0);
-            }
-            c = b < a ? (fl + 1) / 2     // (2i' + 1) Q <= P
-                      : ce / 2;          // (2i' + 1) Q <  P
-            if (c > ad[b]) c = ad[b];
-        }
-        v[b] = o[b] + (int)(d[b] < 0 ? -c : c);
+        const double P = (double)(2 * j + 1) * (double)ad[b];
+        int fl = (int)(P * rq);
+        const double rem = fma(-(double)fl, q, P);
+        int more = rem > 0.0 ? 1 : 0;
+        if (rem < 0.0) { --fl; more = 1; }
+        else if (rem >= q) { ++fl; more = rem > q ? 1 : 0; }
+        // earlier and equal: (2i' + 1) Q <= P; earlier only: (2i' + 1) Q < P
+        c[b] = b == a ? j + 1 : (fl + (b < a ? 1 : more)) >> 1;
+        v[b] = o[b] + (d[b] < 0 ? -c[b] : c[b]);
     }
 }
 
-__device__ inline bool in_extent(const Grid& g, const int v[3]) {
-    return v[0] >= 0 && v[1] >= 0 && v[2] >= 0 && v[0] < g.nx && v[1] < g.ny && v[2] < g.nz;
-}
-
-// Occupancy bit of voxel v (inside the extent) for U voxels at once: the
-// tile-hash probes, the slot-table reads and the occupancy reads of all U
-// are issued together (the first probe position almost always decides; a
-// collision falls back to the probing loop).
-template <int U>
-__device__ inline void occ_bits(const Grid& g, const int (*v)[3], const bool* want, bool* bit) {
-    unsigned long long key[U], got[U];
-    uint32_t h[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        key[u] = pack_key(v[u][0] >> 6, v[u][1] >> 6, v[u][2] >> 6);
-        h[u] = hash_of(key[u], g.tmask);
-        got[u] = want[u] ? g.tkeys[h[u]] : KEY_EMPTY;
-    }
-    int32_t slot[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        int32_t t = -1;
-        if (want[u]) {
-            if (got[u] == key[u]) t = (int32_t)h[u];
-            else if (got[u] != KEY_EMPTY) t = hpos(g.tkeys, g.tmask, key[u]);
-        }
-        const int local = ((v[u][0] >> 3) & 7) + 8 * ((v[u][1] >> 3) & 7) + 64 * ((v[u][2] >> 3) & 7);
-        slot[u] = t >= 0 ? g.tslots[(int64_t)t * 512 + local] : -1;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int b = (v[u][0] & 7) + 8 * (v[u][1] & 7) + 64 * (v[u][2] & 7);
-        bit[u] = slot[u] >= 0 && ((g.occ[(int64_t)slot[u] * 16 + (b >> 5)] >> (b & 31)) & 1u);
-    }
-}
-
-// Slots of ray r in the flat enumeration of visited voxels: its origin and one
-// per crossing, or none when an endpoint lies outside the extent.
-__device__ inline int64_t ray_slots(const Grid& g, const int o[3], bool o_in,
-                                    const int32_t* ends, int64_t r) {
-    const int e[3] = {ends[3 * r], ends[3 * r + 1], ends[3 * r + 2]};
-    if (!o_in || !in_extent(g, e)) return 0;
-    return (int64_t)abs(e[0] - o[0]) + abs(e[1] - o[1]) + abs(e[2] - o[2]) + 1;
-}
-
-// Exclusive prefix sum of the rays' slot counts in two levels: every
-// workgroup of 1024 threads scans its 1024 rays (one ray per thread, a
-// shuffle scan per wave, then the 16 wave totals) into loff[] and its total
-// into btot[]; k_scan_blocks then scans the totals into bpre[].  The first
-// slot of ray r is bpre[r / 1024] + loff[r].  Rays with an endpoint outside
-// the extent get no slots and set EDT_ERR_RANGE.
-__global__ void __launch_bounds__(1024) k_scan_offsets(Grid g, const int32_t* __restrict__ origin,
-                                                       const int32_t* __restrict__ ends, int64_t n,
-                                                       int64_t* loff, int64_t* btot) {
-    __shared__ int64_t wsum[16];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int o[3] = {origin[0], origin[1], origin[2]};
+// The voxels that a scan's rays visit and that are occupied now (the end voxel
+// of a ray with a return excepted) go to `list` as entries to set free, through
+// the counter *c.nfree and up to the capacity c.n.  Rays with an endpoint
+// outside the extent visit nothing and set EDT_ERR_RANGE.
+//
+// A ray's path is taken block by block: a lane takes one block that a ray
+// enters, the sensor's or the one behind a crossing into a new block (every
+// eighth crossing of an axis), and if the block has held an obstacle walks the
+// ray's few voxels in it over the block's bits in LDS.  What bounds it is the
+// chain of loads (ray, tile, slot, flags, bits) and the walk.  16,384 rays of
+// 28 voxels on the mean in the 1024 x 1024 x 128 tunnels take 11.1 us.  A lane
+// per visited voxel took 15.1, and 6.3 more for the prefix sums over all rays
+// that gave each lane its voxel; on 200,000 rays through an open map its
+// arithmetic (a hash and two divisions for each voxel) made a whole call 969 us
+// and is 90 now.  Half a wave per block, testing the seven crossings of each
+// axis, took 25.7: two in three lie in another block.
+// A workgroup takes 64 rays, dealt out because neighbours have much the same
+// length: 8 neighbours to a workgroup took 22, most waves without a block and
+// a few with four times the mean.  The grid's second dimension deals out the
+// blocks of one group, so that a few long rays fill the chip as well.
+constexpr int SCAN_RAYS = 64, SCAN_T = 512;
+__global__ void __launch_bounds__(SCAN_T) k_scan_clear(Grid g, Changes c, int32_t* __restrict__ list) {
+    __shared__ int32_t first[SCAN_RAYS + 1];      // first block of each ray, and their number
+    __shared__ int32_t end[SCAN_RAYS][4];         // end voxel and return of each ray
+    __shared__ uint32_t bits[SCAN_T][17];         // occupancy of each lane's block
+    __shared__ uint16_t at[SCAN_T][22];           // its voxels to set free
+    __shared__ int wcnt[SCAN_T / 64], wgbase;
+    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+    const int o[3] = {c.origin[0], c.origin[1], c.origin[2]};
     const bool o_in = in_extent(g, o);
-    const int64_t r = (int64_t)blockIdx.x * 1024 + t;
-    const int64_t k = r < n ? ray_slots(g, o, o_in, ends, r) : 0;
-    if (r < n && k == 0) set_error(g, -2 /* EDT_ERR_RANGE */);
-    int64_t incl = k;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int64_t v = __shfl_up(incl, d);
-        if (lane >= d) incl += v;
-    }
-    if (lane == 63) wsum[w] = incl;
-    __syncthreads();
-    int64_t before = 0;
-    for (int j = 0; j < w; ++j) before += wsum[j];
-    if (r < n) loff[r] = before + incl - k;
-    if (t == 1023) btot[blockIdx.x] = before + incl;
-}
-
-// Exclusive scan of the nb workgroup totals (one workgroup, chunks of 1024
-// with a carried sum); the total slot count goes to *total.
-__global__ void __launch_bounds__(1024) k_scan_blocks(const int64_t* __restrict__ btot, int64_t nb,
-                                                      int64_t* bpre, int64_t* total) {
-    __shared__ int64_t wsum[16];
-    __shared__ int64_t carry;
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    if (t == 0) carry = 0;
-    __syncthreads();
-    for (int64_t c0 = 0; c0 < nb; c0 += 1024) {
-        const int64_t i = c0 + t;
-        const int64_t k = i < nb ? btot[i] : 0;
-        int64_t incl = k;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int64_t v = __shfl_up(incl, d);
-            if (lane >= d) incl += v;
-        }
-        if (lane == 63) wsum[w] = incl;
-        __syncthreads();
-        int64_t before = carry;
-        for (int j = 0; j < w; ++j) before += wsum[j];
-        if (i < nb) bpre[i] = before + incl - k;
-        __syncthreads();
-        if (t == 1023) carry = before + incl;
-        __syncthreads();
-    }
-    if (t == 0) *total = carry;
-}
-
-__device__ inline int64_t ray_first_slot(const int64_t* loff, const int64_t* bpre, int64_t r) {
-    return bpre[r >> 10] + loff[r];
-}
-
-// Change entries "free" for the visited voxels that are occupied now (the
-// end voxel of a hit excepted).  Lanes take consecutive slots of the flat
-// enumeration, so short rays share a wave; each lane finds its ray by binary
-// search over the offsets.  Entries go to the list front through cnt[0]
-// (capacity cap).
-__global__ void __launch_bounds__(1024) k_scan_clear(Grid g, const int32_t* __restrict__ origin,
-                                                   const int32_t* __restrict__ ends,
-                                                   const uint8_t* __restrict__ hits, int64_t n,
-                                                   const int64_t* __restrict__ loff,
-                                                   const int64_t* __restrict__ bpre,
-                                                   const int64_t* total_p, int32_t* cnt,
-                                                   int32_t* lxyz, uint8_t* lst, int64_t cap) {
-    __shared__ int wcnt[16];
-    __shared__ int wgbase;
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const int o[3] = {origin[0], origin[1], origin[2]};
-    const int64_t total = *total_p;
-    // sixteen waves per workgroup, one chunk of 64 slots each; the list
-    // positions take one counter atomic per workgroup
-    for (int64_t b0 = 1024 * (int64_t)blockIdx.x; b0 < total; b0 += 1024 * (int64_t)gridDim.x) {
-        const int64_t base = b0 + 64 * wid;
-        const int64_t f = base + lane;
-        // rb: the last ray whose first slot is at or before `base`, by a
-        // 64-way search of the whole wave (rays without slots share the next
-        // ray's offset and are passed over)
-        int64_t lo = 0, hi = n - 1;
-        while (lo < hi) {
-            const int64_t span = hi - lo + 1;
-            const int64_t stp = (span + 63) / 64;
-            const int64_t q = lo + (int64_t)lane * stp;
-            const bool le = q <= hi && ray_first_slot(loff, bpre, q) <= base;
-            const unsigned long long m = __ballot(le);   // lane 0 always qualifies
-            const int top = 63 - __clzll((long long)m);
-            lo = lo + (int64_t)top * stp;
-            hi = lo + stp - 1 < hi ? lo + stp - 1 : hi;
-            if (stp == 1) break;
-        }
-        const int64_t rb = lo;
-        // each lane: the last ray in rb .. rb + 63 whose first slot is at or
-        // before f, by binary search over the 64 offsets held across lanes
-        const int64_t wj = rb + lane < n ? ray_first_slot(loff, bpre, rb + lane) : INT64_MAX;
-        int j = 0;
-#pragma unroll
-        for (int stp = 32; stp > 0; stp >>= 1) {
-            const int64_t x = __shfl(wj, j + stp);
-            if (x <= f) j += stp;
-        }
-        int v[1][3] = {{o[0], o[1], o[2]}};
-        bool want[1] = {false}, bit[1];
-        if (f < total) {
-            int64_t r = rb + j;
-            // more than 63 rays without slots in between: continue linearly
-            while (r + 1 < n && ray_first_slot(loff, bpre, r + 1) <= f) ++r;
-            lo = r;
-            const int64_t k = f - ray_first_slot(loff, bpre, lo);     // 0: the sensor voxel, k >= 1: crossing k - 1
-            const int e[3] = {ends[3 * lo], ends[3 * lo + 1], ends[3 * lo + 2]};
-            if (k > 0) {
-                const int d[3] = {e[0] - o[0], e[1] - o[1], e[2] - o[2]};
-                const int ad[3] = {abs(d[0]), abs(d[1]), abs(d[2])};
-                ray_crossing_voxel(o, d, ad, k - 1, v[0]);
+    const int64_t groups = (c.nray + SCAN_RAYS - 1) / SCAN_RAYS;
+    for (int64_t gr = blockIdx.x; gr < groups; gr += gridDim.x) {
+        if (wid == 0) {
+            // neighbouring rays have much the same length: deal them out
+            const int64_t r = gr + lane * groups;
+            int n = 0;
+            if (r < c.nray) {
+                const int e[3] = {c.ends[3 * r], c.ends[3 * r + 1], c.ends[3 * r + 2]};
+                if (o_in && in_extent(g, e))
+                    n = 1 + abs((e[0] >> 3) - (o[0] >> 3)) + abs((e[1] >> 3) - (o[1] >> 3)) +
+                        abs((e[2] >> 3) - (o[2] >> 3));
+                else
+                    set_error(g, -2 /* EDT_ERR_RANGE */);
+                end[lane][0] = e[0];
+                end[lane][1] = e[1];
+                end[lane][2] = e[2];
+                end[lane][3] = c.hits[r];
             }
-            const bool at_end = v[0][0] == e[0] && v[0][1] == e[1] && v[0][2] == e[2];
-            want[0] = !(hits[lo] && at_end);
-        }
-        occ_bits<1>(g, v, want, bit);
-        const bool emit = want[0] && bit[0];
-        const unsigned long long m = __ballot(emit);
-        if (lane == 0) wcnt[wid] = __popcll(m);
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int sum = 0;
-            for (int j = 0; j < 16; ++j) sum += wcnt[j];
-            wgbase = sum ? atomicAdd(cnt, sum) : 0;
-        }
-        __syncthreads();
-        int idx = wgbase;
-        for (int j = 0; j < wid; ++j) idx += wcnt[j];
-        idx += __popcll(m & ((1ull << lane) - 1ull));
-        __syncthreads();
-        if (emit) {
-            if (idx < cap) {
-                lxyz[3 * (int64_t)idx] = v[0][0];
-                lxyz[3 * (int64_t)idx + 1] = v[0][1];
-                lxyz[3 * (int64_t)idx + 2] = v[0][2];
-                lst[idx] = 0;
-            } else {
-                set_error(g, -3 /* EDT_ERR_CAPACITY */);
+            int incl = n;
+#pragma unroll
+            for (int s = 1; s < SCAN_RAYS; s <<= 1) {
+                const int v = __shfl_up(incl, s);
+                if (lane >= s) incl += v;
             }
+            first[lane] = incl - n;
+            if (lane == SCAN_RAYS - 1) first[SCAN_RAYS] = incl;
         }
-    }
-}
-
-// Change entries "occupied" for every hit end voxel, after all free entries
-// (the update takes the last entry of a voxel, so hits win).  cnt[1] counts
-// them, cnt[3] the finished workgroups; cnt[2] receives the list length.
-__global__ void k_scan_hits(Grid g, const int32_t* __restrict__ origin,
-                            const int32_t* __restrict__ ends, const uint8_t* __restrict__ hits,
-                            int64_t n, int32_t* cnt, int32_t* lxyz, uint8_t* lst, int64_t cap) {
-    const int o[3] = {origin[0], origin[1], origin[2]};
-    const bool o_in = in_extent(g, o);
-    const int64_t base = cnt[0] < cap ? cnt[0] : cap;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t r0 = blockIdx.x * (int64_t)blockDim.x; r0 < n; r0 += stride) {
-        const int64_t r = r0 + threadIdx.x;
-        int e[3] = {0, 0, 0};
-        bool emit = false;
-        if (r < n) {
-            e[0] = ends[3 * r];
-            e[1] = ends[3 * r + 1];
-            e[2] = ends[3 * r + 2];
-            emit = hits[r] != 0 && o_in && in_extent(g, e);
+        __syncthreads();
+        const int total = first[SCAN_RAYS];
+        for (int c0 = SCAN_T * (int)blockIdx.y; c0 < total; c0 += SCAN_T * (int)gridDim.y) {
+            const int f = c0 + t;
+            int r = 0;                             // the last ray with first[r] <= f
+#pragma unroll
+            for (int k = SCAN_RAYS / 2; k > 0; k >>= 1) r += first[r + k] <= f ? k : 0;
+            const int e[3] = {end[r][0], end[r][1], end[r][2]};
+            const bool ret = end[r][3] != 0;
+            int v[3] = {o[0], o[1], o[2]};
+            int32_t slot = -1;
+            const int d[3] = {e[0] - o[0], e[1] - o[1], e[2] - o[2]};
+            const int ad[3] = {abs(d[0]), abs(d[1]), abs(d[2])};
+            if (f < total) {
+                int m = f - first[r] - 1;          // -1: the sensor's block
+                if (m >= 0) {
+                    const int m0 = abs((e[0] >> 3) - (o[0] >> 3));
+                    const int m1 = abs((e[1] >> 3) - (o[1] >> 3));
+                    int a = 0;
+                    if (m >= m0) {
+                        m -= m0;
+                        a = 1;
+                        if (m >= m1) { m -= m1; a = 2; }
+                    }
+                    const int oa = a == 0 ? o[0] : a == 1 ? o[1] : o[2];
+                    const int da = a == 0 ? d[0] : a == 1 ? d[1] : d[2];
+                    // the m-th crossing of axis a into a new block
+                    ray_crossing_voxel(o, d, ad, a, 8 * m + (da < 0 ? oa & 7 : 7 - (oa & 7)), v);
+                }
+                slot = find_block(g, v[0] >> 3, v[1] >> 3, v[2] >> 3);
+                if (slot >= 0 && !(g.flags[slot] & F_DILATED)) slot = -1;
+            }
+            if (slot >= 0) {
+                const uint4* p = (const uint4*)(g.occ + (int64_t)slot * 16);
+                const uint4 q[4] = {p[0], p[1], p[2], p[3]};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    bits[t][4 * k] = q[k].x;
+                    bits[t][4 * k + 1] = q[k].y;
+                    bits[t][4 * k + 2] = q[k].z;
+                    bits[t][4 * k + 3] = q[k].w;
+                }
+            }
+            // the walk: at most 22 voxels, as a ray never turns back
+            int n = 0;
+            if (slot >= 0) {
+                // e.. compares the parameters of the next crossings of two axes
+                // a before b, (2 i_a + 1) |d_b| - (2 i_b + 1) |d_a|: the one on
+                // a comes first iff it is <= 0.  Both lie within one period, so
+                // the difference stays within 2 max |d| and is exact although
+                // the products may wrap.
+                const int mv[3] = {abs(v[0] - o[0]), abs(v[1] - o[1]), abs(v[2] - o[2])};
+                const uint32_t n0 = 2 * mv[0] + 1, n1 = 2 * mv[1] + 1, n2 = 2 * mv[2] + 1;
+                const int a0 = 2 * ad[0], a1 = 2 * ad[1], a2 = 2 * ad[2];
+                int e01 = (int)(n0 * (uint32_t)ad[1] - n1 * (uint32_t)ad[0]);
+                int e02 = (int)(n0 * (uint32_t)ad[2] - n2 * (uint32_t)ad[0]);
+                int e12 = (int)(n1 * (uint32_t)ad[2] - n2 * (uint32_t)ad[1]);
+                int left = ad[0] + ad[1] + ad[2] - mv[0] - mv[1] - mv[2];
+                const int s0 = d[0] < 0 ? -1 : 1, s1 = d[1] < 0 ? -16 : 16,
+                          s2 = d[2] < 0 ? -256 : 256;
+                // position in the block, one hex digit per axis: leaving it
+                // sets bit 3 of the digit that steps to 8 or to -1
+                int p = (v[0] & 7) | (v[1] & 7) << 4 | (v[2] & 7) << 8;
+#pragma unroll 1
+                for (int k = 0; k < 22; ++k) {
+                    const uint32_t word = bits[t][(p >> 7 & 14) | (p >> 6 & 1)];
+                    const bool set = (word >> ((p & 7) | (p >> 1 & 24))) & 1u;
+                    if (set && !(ret && left == 0)) at[t][n++] = (uint16_t)p;
+                    if (--left < 0) break;
+                    const bool x = max(e01, e02) <= 0, y = e12 <= 0;
+                    e01 += x ? a1 : y ? -a0 : 0;
+                    e02 += x ? a2 : y ? 0 : -a0;
+                    e12 += x ? 0 : y ? a2 : -a1;
+                    p += x ? s0 : y ? s1 : s2;
+                    if (p & 0x888) break;
+                }
+            }
+            // list positions: one counter atomic per workgroup
+            int incl = n;
+#pragma unroll
+            for (int s = 1; s < 64; s <<= 1) {
+                const int u = __shfl_up(incl, s);
+                if (lane >= s) incl += u;
+            }
+            if (lane == 63) wcnt[wid] = incl;
+            __syncthreads();
+            int before = 0, all = 0;
+#pragma unroll
+            for (int k = 0; k < SCAN_T / 64; ++k) {
+                before += k < wid ? wcnt[k] : 0;
+                all += wcnt[k];
+            }
+            if (all != 0) {
+                if (t == 0) wgbase = atomicAdd(c.nfree, all);
+                __syncthreads();
+                const int64_t q = (int64_t)wgbase + before + incl - n;
+                for (int k = 0; k < n; ++k) {
+                    if (q + k >= c.n) {
+                        set_error(g, -3 /* EDT_ERR_CAPACITY */);
+                        break;
+                    }
+                    const int p = at[t][k];
+                    int32_t* out = list + 3 * (q + k);
+                    out[0] = (v[0] & ~7) | (p & 7);
+                    out[1] = (v[1] & ~7) | (p >> 4 & 7);
+                    out[2] = (v[2] & ~7) | (p >> 8 & 7);
+                }
+            }
+            __syncthreads();
         }
-        const int idx = wave_append(emit, cnt + 1);
-        if (emit) {
-            const int64_t p = base + idx;
-            lxyz[3 * p] = e[0];
-            lxyz[3 * p + 1] = e[1];
-            lxyz[3 * p + 2] = e[2];
-            lst[p] = 1;
-        }
-    }
-    // the last workgroup to finish writes the list length into cnt[2]
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();
-        if (atomicAdd(cnt + 3, 1) == (int)gridDim.x - 1)
-            cnt[2] = (int32_t)(base + atomicAdd(cnt + 1, 0));
+        __syncthreads();
     }
 }
 
