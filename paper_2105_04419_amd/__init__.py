@@ -140,8 +140,12 @@ def _check(where, rc):
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    """Handle of `stream`, or of the current device's current stream (without
+    the Stream object of torch.cuda.current_stream(): 0.2 instead of 3.0 us a
+    call, and 7 us on autograd's thread)."""
+    if stream is not None:
+        return ctypes.c_void_p(stream.cuda_stream)
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
 
 
 def _ptr(t):
@@ -497,42 +501,63 @@ def dense_global_noalloc(occ: torch.Tensor, d_max: int = 0, out: torch.Tensor | 
 # ---------------------------------------------------------------------------
 # clearance cost
 # ---------------------------------------------------------------------------
+def _clearance_shapes(s, wp):
+    if s.dim() != 3:
+        raise ValueError("field must be (nz, ny, nx)")
+    if wp.dim() != 3 or wp.shape[-1] != 3:
+        raise ValueError("waypoints must be (T, W, 3)")
+
+
 def _clearance_args(s, wp):
     if s.dim() != 3:
         raise ValueError("field must be (nz, ny, nx)")
     s = _dev_tensor(s, torch.int32)
     wp = _dev_tensor(wp, torch.float32)
-    if wp.dim() != 3 or wp.shape[-1] != 3:
-        raise ValueError("waypoints must be (T, W, 3)")
+    _clearance_shapes(s, wp)
+    return s, wp
+
+
+# The calls themselves, on arguments that _clearance_args has passed and an
+# output of the right type and shape.  A cost and its gradient are 12 us of
+# kernels, so the time of the pair is this host path: checked once, it went
+# from 118 to 79 us (4096 trajectories of 64 waypoints) with the stream's
+# handle taken directly.
+def _clearance_fwd(s, wp, h, margin, out, stream=None):
     nz, ny, nx = s.shape
-    return s, wp, nx, ny, nz
+    T, W, _ = wp.shape
+    _check("edt_clearance_fwd", lib().edt_clearance_fwd(
+        s.data_ptr(), nx, ny, nz, h, margin, wp.data_ptr(), T, W, out.data_ptr(), _stream(stream)))
+    return out
+
+
+def _clearance_bwd(s, wp, gcost, h, margin, out, stream=None):
+    nz, ny, nx = s.shape
+    T, W, _ = wp.shape
+    if gcost.dtype != torch.float32:
+        gcost = gcost.to(torch.float32)
+    gcost = _dev_tensor(gcost, torch.float32, (T,))
+    _check("edt_clearance_bwd", lib().edt_clearance_bwd(
+        s.data_ptr(), nx, ny, nz, h, margin, wp.data_ptr(), T, W, gcost.data_ptr(),
+        out.data_ptr(), _stream(stream)))
+    return out
 
 
 def clearance_fwd(s, wp, h: float, margin: float, out=None, stream=None):
     """edt_clearance_fwd: per-trajectory cost (float32 [T]) of waypoints
     wp (T, W, 3) on the int32 field s (nz, ny, nx), no autograd."""
-    s, wp, nx, ny, nz = _clearance_args(s, wp)
-    T, W = int(wp.shape[0]), int(wp.shape[1])
-    if out is None:
-        out = torch.empty(T, dtype=torch.float32, device=wp.device)
-    out = _dev_tensor(out, torch.float32, (T,))
-    _check("edt_clearance_fwd", lib().edt_clearance_fwd(
-        _ptr(s), nx, ny, nz, float(h), float(margin), _ptr(wp), T, W, _ptr(out), _stream(stream)))
-    return out
+    s, wp = _clearance_args(s, wp)
+    T = int(wp.shape[0])
+    out = (torch.empty(T, dtype=torch.float32, device=wp.device) if out is None
+           else _dev_tensor(out, torch.float32, (T,)))
+    return _clearance_fwd(s, wp, float(h), float(margin), out, stream)
 
 
 def clearance_bwd(s, wp, gcost, h: float, margin: float, out=None, stream=None):
     """edt_clearance_bwd: gcost[t] * d C[t] / d wp (float32 (T, W, 3))."""
-    s, wp, nx, ny, nz = _clearance_args(s, wp)
-    T, W = int(wp.shape[0]), int(wp.shape[1])
-    gcost = _dev_tensor(gcost.to(torch.float32), torch.float32, (T,))
-    if out is None:
-        out = torch.empty_like(wp)
-    out = _dev_tensor(out, torch.float32, tuple(wp.shape))
-    _check("edt_clearance_bwd", lib().edt_clearance_bwd(
-        _ptr(s), nx, ny, nz, float(h), float(margin), _ptr(wp), T, W, _ptr(gcost), _ptr(out),
-        _stream(stream)))
-    return out
+    s, wp = _clearance_args(s, wp)
+    out = (torch.empty_like(wp) if out is None
+           else _dev_tensor(out, torch.float32, tuple(wp.shape)))
+    return _clearance_bwd(s, wp, gcost, float(h), float(margin), out, stream)
 
 
 class ClearanceCost(torch.autograd.Function):
@@ -543,15 +568,19 @@ class ClearanceCost(torch.autograd.Function):
     def forward(ctx, s, wp, h: float, margin: float):
         s = _dev_tensor(s, torch.int32)
         wp = _dev_tensor(wp, torch.float32)
-        cost = clearance_fwd(s, wp, h, margin)
+        _clearance_shapes(s, wp)
+        h, margin = float(h), float(margin)
+        cost = torch.empty(wp.shape[0], dtype=torch.float32, device=wp.device)
+        _clearance_fwd(s, wp, h, margin, cost)
         ctx.save_for_backward(s, wp)
-        ctx.h, ctx.margin = float(h), float(margin)
+        ctx.h, ctx.margin = h, margin
         return cost
 
     @staticmethod
     def backward(ctx, gcost):
-        s, wp = ctx.saved_tensors
-        return None, clearance_bwd(s, wp, gcost.contiguous(), ctx.h, ctx.margin), None, None
+        # the saved tensors may have been through a caller's hooks
+        s, wp = _clearance_args(*ctx.saved_tensors)
+        return None, _clearance_bwd(s, wp, gcost, ctx.h, ctx.margin, torch.empty_like(wp)), None, None
 
 
 def clearance_cost(s, wp, h: float = 0.2, margin: float = 1.0):
