@@ -666,7 +666,6 @@ edt_status edt_interior(edt_ctx* c, void* stream) {
     const Grid& g = c->g;
     if (g.max_int <= 0) return EDT_ERR_STATE;
     hipStream_t st = S(stream);
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, g.cnt + C_NINT, (int64_t)1, 0);
     hipLaunchKernelGGL(k_int_list, dim3(grid_for(g.max_blocks, 256, 16384)), dim3(64), 0, st, g);
     const int grid = grid_for(g.max_int, 1, 16384);
     hipLaunchKernelGGL(k_int_x, dim3(grid), dim3(64), 0, st, g);

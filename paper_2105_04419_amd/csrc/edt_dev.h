@@ -54,7 +54,7 @@ enum : uint32_t {
 // cancelled (read by the first three kernels of the update, cleared by the
 // fourth, so a captured update replays with the same arguments).
 enum {
-    C_NBLK = 0, C_NDIL, C_ERR, C_ABORT, C_NINT, C_UABORT,
+    C_NBLK = 0, C_NDIL, C_ERR, C_ABORT, C_NINT, C_UABORT, C_INTN,
     C_NYI, C_NZI, C_NADD, C_NREM, C_NSEED, C_NDIRTY, C_NRAISE, C_NLOWER,
     C_NXS, C_NYS, C_NNEWDIL, C_DONE, C_NTILE, C_N
 };

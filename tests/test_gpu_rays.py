@@ -12,6 +12,11 @@ from paper_2105_04419_amd import EDT_ERR_CAPACITY, Field
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module", autouse=True)
+def _setup():
+    oracle.build(force=False)
+
+
 def dev(a, dtype):
     return torch.from_numpy(np.ascontiguousarray(a).astype(dtype)).cuda()
 
