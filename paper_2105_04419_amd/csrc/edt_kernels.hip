@@ -1144,6 +1144,10 @@ __device__ inline uint32_t s_pair_int(const Grid& g, uint32_t w) {
                         : w;
 }
 
+__device__ inline void store_through(uint16_t* p, uint16_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Stores the results of one step of the windowed minimum: acc[o] holds output
 // row o of two consecutive blocks (low half: slot0, high half: slot1; a
 // negative slot has no storage and its half is dropped).  Pass Y writes g2
@@ -1177,19 +1181,21 @@ __device__ inline void win_store(const Grid& g, int32_t slot0, int32_t slot1, co
     } else {
         // s goes through the caches: what follows a transform reads it, and
         // finds it in the last-level cache (tunnel extent at d_max 32: dense
-        // readback 131 -> 102 us; non-temporal stores made pass Z itself 1.5 us
-        // of 55 faster)
+        // readback 131 -> 102 us; non-temporal stores, which pass that cache by,
+        // made the transform alone 159.3 us).  It is written through the L2
+        // (system scope), which leaves that to the g2 still to be read: 160.8 us
+        // for 161.9 with plain stores.
         const uint32_t m = wave_reduce_pk_u16<true>(as_u32(max8<F16>(acc)));
         if (slot0 >= 0) {
             uint16_t* d0 = g.s + (int64_t)slot0 * 512 + lane;
 #pragma unroll
-            for (int o = 0; o < 8; ++o) d0[64 * o] = acc[o].x;
+            for (int o = 0; o < 8; ++o) store_through(&d0[64 * o], acc[o].x);
             if (lane == 0) g.bmax[slot0] = F16 ? f16_int(m & 0xffffu) : (int)(m & 0xffffu);
         }
         if (slot1 >= 0) {
             uint16_t* d1 = g.s + (int64_t)slot1 * 512 + lane;
 #pragma unroll
-            for (int o = 0; o < 8; ++o) d1[64 * o] = acc[o].y;
+            for (int o = 0; o < 8; ++o) store_through(&d1[64 * o], acc[o].y);
             if (lane == 0) g.bmax[slot1] = F16 ? f16_int(m >> 16) : (int)(m >> 16);
         }
     }
