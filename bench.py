@@ -153,7 +153,8 @@ def roofline(g, dmax):
     R = (dmax + 7) // 8
     names = ({"pass_x": f"k_pass_x_rows<{R}>", "pass_y": f"k_pass_win_tiles<{R},1>",
               "pass_z": f"k_pass_win_tiles<{R},2>"} if R <= 8 else
-             {"pass_x": "k_pass_x", "pass_y": "k_pass_y", "pass_z": "k_pass_z"})
+             {"pass_x": "k_pass_x_rows_wide", "pass_y": "k_pass_hull<1>",
+              "pass_z": "k_pass_hull<2>"})
     kern = g["dominant"]
     ms = g["dominant_ms"]
     achieved = per_launch[kern] / (ms * 1e-3) / 1e9

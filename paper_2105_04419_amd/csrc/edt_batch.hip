@@ -388,7 +388,8 @@ __device__ inline void item_y(const BArgs& a, const MapDev& m, int li, uint32_t 
 // 512 bytes, at 5.4 in aligned ones).  So an item stores, of every plane, the
 // lines that start among its own voxels: its last 20 pairs are also the next
 // item's first, eight rows go through LDS in the plane's order, and the lanes
-// take them from there two by two from the first line's start on.
+// take them from there two by two from the first line's start on: 322 -> 271
+// us on 206 M voxels, for 45% more columns to compute.
 constexpr int ZROW = 132;                      // LDS halfwords of a row (130, 131: unused pairs)
 // (a lane reads up to halfword 31 + 2 * 63 + 1 of its row before it drops what
 // lies past the item: 26 past the last row)
