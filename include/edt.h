@@ -367,7 +367,7 @@ edt_status edt_dense_global_noalloc(int32_t nx, int32_t ny, int32_t nz, int32_t 
  * edt_dense_global (paper section IV-B, Algorithm 1's SetObstacle /
  * RemoveObstacle followed by DistanceTransform, with d_max = infinity as in
  * its section V-B runs).  The context holds the occupancy (uint8 per voxel),
- * both int32 intermediates and the int32 field in the caller's workspace
+ * both intermediates and the int32 field in the caller's workspace
  * (256-byte aligned, edt_dense_ctx_bytes bytes; about 21 bytes per voxel);
  * it is owned by the caller and must outlive the context.  d_max: 0 = no
  * limit (voxels of a map without obstacles read EDT_DENSE_INF), else

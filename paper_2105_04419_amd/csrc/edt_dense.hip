@@ -949,7 +949,9 @@ bool dense_layout(int32_t nx, int32_t ny, int32_t nz, int64_t max_changes, Dense
     int64_t o = 0;
     auto take = [&](int64_t bytes) { const int64_t at = o; o += (bytes + 255) & ~(int64_t)255; return at; };
     L->occ = take(n);
-    L->g1 = take(4 * n);
+    // int32 distances or row records; a row of one voxel has a record of 8 bytes
+    const int64_t records = 8 * nxc * ny * nz;
+    L->g1 = take(records > 4 * n ? records : 4 * n);
     L->g2 = take(4 * n);
     L->s = take(4 * n);
     L->env = take(8 * n);

@@ -95,6 +95,20 @@ def test_dense_context_validates_without_touching_the_gpu(L):
     assert L.edt_dense_ctx_get_error(None, None) == -1
 
 
+def test_dense_context_holds_its_regions(L):
+    # the regions of a context, side by side: occupancy, pass x (int32 per
+    # voxel, or 8 bytes per 32 voxels of a row, more where a row is one voxel),
+    # pass y, the field, the envelopes, the marks and the dedupe table
+    for nx, ny, nz in [(1, 200, 70), (1, 1000, 33), (1, 1, 4000), (1, 1100, 3), (2, 200, 70),
+                       (33, 40, 50)]:
+        n, words, changes = nx * ny * nz, (nx + 31) // 32, 100
+        rows = ny * nz
+        x = max(4 * n, 8 * words * rows)
+        marks = 8 * rows + 8 * words * (ny + nz)
+        table = 12 * 256 + 4 * changes
+        assert L.edt_dense_ctx_bytes(nx, ny, nz, changes) >= 17 * n + x + marks + table, (nx, ny, nz)
+
+
 def test_product_package_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2105_04419_amd")
     for dirpath, _, files in os.walk(pkg):

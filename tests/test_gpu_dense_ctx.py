@@ -76,6 +76,24 @@ def test_updates_match_the_oracle(shape, d_max):
     assert f.error() == 0
 
 
+@pytest.mark.parametrize("shape", [(1, 200, 70), (1, 1000, 33), (1, 1, 400), (1, 33, 1),
+                                   (1, 1025, 3), (2, 200, 70)])
+def test_rows_of_one_voxel(shape):
+    # their records take more room than their distances
+    nx, ny, nz = shape
+    rng = np.random.default_rng(ny + nz)
+    occ = (rng.random((nz, ny, nx)) < 0.01).astype(np.uint8)
+    f = DenseField(shape, 0, max_changes=64)
+    f.global_(cu(occ))
+    same(f.field().cpu().numpy(), ref(occ, 0), f"{shape} global")
+    for step in range(4):
+        xyz, st = random_changes(rng, occ, 40, 0.5)
+        f.update(cu(xyz), cu(st))
+        apply(occ, xyz, st)
+        same(f.field().cpu().numpy(), ref(occ, 0), f"{shape} step {step}")
+    assert f.error() == 0
+
+
 def test_remove_every_obstacle_then_add_one():
     nx, ny, nz = 40, 30, 20
     occ = np.zeros((nz, ny, nx), np.uint8)
