@@ -282,7 +282,10 @@ typedef struct {
 } edt_batch_map;
 
 /* Schedule of a batched run (edt_batch_run; NULL = defaults {8, 8, 4, 0, 4}):
- *   lrun          blocks per work item along y and z (1 .. 64)
+ *   lrun          most blocks per work item along y and z (1 .. 64); halved
+ *                 while the items of a launch would leave most of the GPU
+ *                 without a wave (in PER_MAP a launch holds one map's items,
+ *                 so its runs may be shorter than the other modes')
  *   waves_per_cu  waves resident per compute unit (0 = default, <= 64)
  *   chunk         work items taken per queue atomic (1 .. 1024)
  *   schedule      0 = dynamic queue, 1 = static stride
@@ -321,7 +324,11 @@ int64_t edt_batch_workspace_bytes(const edt_batch_map* maps, int32_t n_maps, int
 edt_status edt_batch_create(const edt_batch_map* maps, int32_t n_maps, int32_t d_max,
                             void* d_ws, int64_t ws_bytes, void* stream, edt_batch** out);
 
-/* Transforms every map of the batch (mode: edt_batch_mode). */
+/* Transforms every map of the batch (mode: edt_batch_mode).  The workspace
+ * keeps the item tables of the last run length, one set for PER_MAP and one
+ * for the other two modes; a run of another lrun rebuilds its set.  So a run
+ * to be captured follows one of the same mode and tune, and between its
+ * replays the batch runs no other lrun in that set's modes. */
 edt_status edt_batch_run(edt_batch* batch, const uint8_t* d_occ, int32_t* d_out,
                          int32_t mode, const edt_tune* tune, void* stream);
 

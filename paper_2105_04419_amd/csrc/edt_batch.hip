@@ -622,8 +622,13 @@ __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
 
 int64_t align256(int64_t v) { return (v + 255) & ~(int64_t)255; }
 
+// Two sets of item tables, for the launches over all maps (FUSED, PHASED) and
+// for those per map: each kind picks its own run length, and a captured run
+// reads its set again at every replay, whatever the other kind has run since.
+constexpr int TABLES = 2;
+
 struct BLayout {
-    int64_t off_maps, off_pref, off_queues, off_itemmap, off_g1, off_g2, total;
+    int64_t off_maps, off_pref[TABLES], off_queues, off_itemmap[TABLES], off_g1, off_g2, total;
     int64_t icap;            // item-map entries per phase
 };
 
@@ -663,9 +668,11 @@ bool blayout(const edt_batch_map* maps, int n, int dmax, BLayout* L) {
     if (nb > (1ll << 26)) return false;
     int64_t o = 0;
     L->off_maps = o; o += align256((int64_t)n * sizeof(MapDev));
-    L->off_pref = o; o += align256((int64_t)3 * (n + 1) * 4);
+    for (int t = 0; t < TABLES; ++t) {
+        L->off_pref[t] = o; o += align256((int64_t)3 * (n + 1) * 4);
+        L->off_itemmap[t] = o; o += align256(3 * icap * 4);
+    }
     L->off_queues = o; o += align256((int64_t)3 * (n + 1) * 4);
-    L->off_itemmap = o; o += align256(3 * icap * 4);
     L->icap = icap;
     L->off_g1 = o; o += align256(pairs * 2);
     L->off_g2 = o; o += align256(pairs2 * 4);
@@ -686,7 +693,7 @@ struct edt_batch {
     BLayout L;
     char* ws;
     MapDev* host_maps;       // in processing order
-    int last_lrun;
+    int last_lrun[TABLES];   // run length that each set of item tables is for
     int cus;
 };
 
@@ -821,7 +828,6 @@ edt_status edt_batch_create(const edt_batch_map* maps, int32_t n_maps, int32_t d
         free(b);
         return EDT_ERR_HIP;
     }
-    b->last_lrun = 0;
     *out = b;
     return EDT_OK;
 }
@@ -849,7 +855,8 @@ edt_status edt_batch_run(edt_batch* b, const uint8_t* d_occ, int32_t* d_out, int
     const BLayout& L = b->L;
     BArgs a;
     a.maps = (const MapDev*)(b->ws + L.off_maps);
-    a.pref = (const int32_t*)(b->ws + L.off_pref);
+    const int table = mode == EDT_BATCH_PER_MAP ? 1 : 0;
+    a.pref = (const int32_t*)(b->ws + L.off_pref[table]);
     a.queues = (int32_t*)(b->ws + L.off_queues);
     a.occ = d_occ;
     a.out = d_out;
@@ -862,7 +869,7 @@ edt_status edt_batch_run(edt_batch* b, const uint8_t* d_occ, int32_t* d_out, int
     a.lrun = t.lrun;
     a.chunk = t.chunk;
     a.schedule = t.schedule;
-    a.itemmap = (const int32_t*)(b->ws + L.off_itemmap);
+    a.itemmap = (const int32_t*)(b->ws + L.off_itemmap[table]);
     a.icap = L.icap;
     // shorter runs while the items of a launch would leave most of the GPU
     // without a wave: a run is walked in order, about 1.5 us per 8 rows, and two
@@ -875,14 +882,14 @@ edt_status edt_batch_run(edt_batch* b, const uint8_t* d_occ, int32_t* d_out, int
     };
     while (a.lrun > 1 && runs(a.lrun) < (int64_t)b->cus * 8) a.lrun = (a.lrun + 1) / 2;
     // item offsets and the item -> map table depend on the run length only:
-    // rebuilt when it changes; the dynamic schedule's grab counters start at
+    // rebuilt when it changes for the mode's set; the dynamic schedule's grab counters start at
     // zero on every run
-    if (a.lrun != b->last_lrun) {
+    if (a.lrun != b->last_lrun[table]) {
         hipLaunchKernelGGL(k_batch_prefix, dim3(1), dim3(1024), 0, st, a.maps, b->n, a.lrun,
                            (int32_t*)a.pref);
         hipLaunchKernelGGL(k_batch_itemmap, dim3(b->n), dim3(256), 0, st, a.pref, b->n,
                            (int32_t*)a.itemmap, a.icap);
-        b->last_lrun = a.lrun;
+        b->last_lrun[table] = a.lrun;
     }
     if (t.schedule == 0)
         hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, st, (uint32_t*)a.queues,

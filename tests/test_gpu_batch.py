@@ -147,6 +147,32 @@ def test_run_length_changes_between_runs():
         assert torch.equal(b.run(occ, mode=PHASED, tune=t), ref), lrun
 
 
+@pytest.mark.parametrize("captured,between", [(PER_MAP, PHASED), (PHASED, PER_MAP)])
+def test_a_captured_run_keeps_its_run_length(captured, between):
+    # one tune gives launches per map shorter runs than launches over all maps;
+    # a run of the other kind leaves a captured run's item tables alone
+    rng = np.random.default_rng(8)
+    maps = [(rng.random((64, 40, 48)) < 0.01).astype(np.uint8) for _ in range(96)]
+    b = Batch([(48, 40, 64)] * len(maps), 12)
+    occ = b.pack(maps)
+    tune = {"lrun": 16, "chunk": 4, "schedule": 1, "waves_per_cu": 8, "wg_waves": 4}
+    out = torch.empty(b.total, dtype=torch.int32, device="cuda")
+    other = torch.empty_like(out)
+    b.run(occ, out=out, mode=captured, tune=tune)
+    ref = out.clone()
+    check(b, maps[:4], ref, 12, "eager")
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        b.run(occ, out=out, mode=captured, tune=tune)
+    for replay in range(3):
+        b.run(occ, out=other, mode=between, tune=tune)
+        out.fill_(-7)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(other, ref) and torch.equal(out, ref), replay
+
+
 def test_autotuner_picks_a_launch_mode_and_schedule(tmp_path, monkeypatch):
     from paper_2105_04419_amd import autotune
     monkeypatch.setenv("VDBEDT_CACHE", str(tmp_path))
