@@ -71,3 +71,22 @@ def test_occupancy_and_field_at_any_address():
         b.run(occ[off:off + b.total], out=out[off:off + b.total], mode=PHASED)
         check(b, maps, out[off:off + b.total], 24, off)
         assert (out[:off] == -7).all() and (out[off + b.total:] == -7).all()
+
+
+@pytest.mark.parametrize("d_max", [8, 9, 24, 40, 41, 64])
+def test_items_out_of_reach(d_max):
+    # one obstacle a map, at every distance from the items (runs of 1 or 2 blocks)
+    # along y and z: items just within its reach, at its end and beyond it
+    shapes, maps = [], []
+    for k in range(0, 200, 5):
+        for axis in (0, 1):
+            nz, ny, nx = (200, 3, 18) if axis == 0 else (3, 200, 18)
+            occ = np.zeros((nz, ny, nx), np.uint8)
+            occ[(k, 1, 7) if axis == 0 else (1, k, 7)] = 1
+            shapes.append((nx, ny, nz))
+            maps.append(occ)
+    b = Batch(shapes, d_max)
+    for lrun in (1, 16):
+        out = b.run(b.pack(maps), mode=PHASED, tune={"lrun": lrun, "schedule": 1})
+        for sh, occ, got in zip(shapes, maps, b.unpack(out)):
+            assert np.array_equal(got.cpu().numpy(), oracle.edt_separable(occ, d_max)), (sh, lrun)
