@@ -728,10 +728,29 @@ struct edt_batch {
     char* ws;
     MapDev* host_maps;       // in processing order
     int last_lrun[TABLES];   // run length that each set of item tables is for
+    int lrun[TABLES][65];    // run length taken for a caller's, per set
     int cus;
 };
 
 namespace {
+
+// Run lengths: the caller's, halved while the items of a launch would leave
+// most of the GPU without a wave: a run is walked in order, about 1.5 us per 8
+// rows, and two maps of 64 voxels a side have 64 runs of 16 blocks, 512 of one
+// (27.8 -> 15.3 us; 5 maps of up to 256: 82 -> 71 us).  A PER_MAP launch has
+// one map's items (the mean map's here).  Told once, when the batch is made: a
+// walk over 65,536 maps takes the host 79 us.
+void run_lengths(edt_batch* b) {
+    int64_t runs[65] = {};
+    for (int i = 0; i < b->n; ++i)
+        for (int l = 1; l <= 64; ++l) runs[l] += phase_items(b->host_maps[i], 1, l);
+    for (int t = 0; t < TABLES; ++t)
+        for (int l = 1; l <= 64; ++l) {
+            int e = l;
+            while (e > 1 && runs[e] / (t == 0 ? 1 : b->n) < (int64_t)b->cus * 8) e = (e + 1) / 2;
+            b->lrun[t][l] = e;
+        }
+}
 
 template <bool F16>
 edt_status launch_batch(edt_batch* b, const BArgs& a, int mode, int waves_per_cu, int wg_waves,
@@ -850,6 +869,7 @@ edt_status edt_batch_create(const edt_batch_map* maps, int32_t n_maps, int32_t d
         free(b);
         return EDT_ERR_HIP;
     }
+    run_lengths(b);
     hipStream_t st = (hipStream_t)stream;
     if (hipMemcpyAsync(b->ws + L.off_maps, b->host_maps, sizeof(MapDev) * (size_t)n_maps,
                        hipMemcpyHostToDevice, st) != hipSuccess) {
@@ -900,21 +920,11 @@ edt_status edt_batch_run(edt_batch* b, const uint8_t* d_occ, int32_t* d_out, int
     a.dmax = b->dmax;
     a.D = b->dmax * b->dmax;
     a.M = (b->dmax + 7) / 8;
-    a.lrun = t.lrun;
+    a.lrun = b->lrun[table][t.lrun];
     a.chunk = t.chunk;
     a.schedule = t.schedule;
     a.itemmap = (const int32_t*)(b->ws + L.off_itemmap[table]);
     a.icap = L.icap;
-    // shorter runs while the items of a launch would leave most of the GPU
-    // without a wave: a run is walked in order, about 1.5 us per 8 rows, and two
-    // maps of 64 voxels a side have 64 runs of 16 blocks, 512 of one (27.8 ->
-    // 15.3 us; 5 maps of up to 256: 82 -> 71 us)
-    auto runs = [&](int lrun) {
-        int64_t n = 0;
-        for (int i = 0; i < b->n; ++i) n += phase_items(b->host_maps[i], 1, lrun);
-        return mode == EDT_BATCH_PER_MAP ? n / b->n : n;
-    };
-    while (a.lrun > 1 && runs(a.lrun) < (int64_t)b->cus * 8) a.lrun = (a.lrun + 1) / 2;
     // item offsets and the item -> map table depend on the run length only:
     // rebuilt when it changes for the mode's set; the dynamic schedule's grab counters start at
     // zero on every run

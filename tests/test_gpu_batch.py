@@ -1,6 +1,8 @@
 """Batched transform of many dense maps: the fused persistent launch, the
 launch per pass, the per-map launches and the CPU oracle agree bit for bit
 on every map, for every schedule the autotuner may pick."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -171,6 +173,24 @@ def test_a_captured_run_keeps_its_run_length(captured, between):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(other, ref) and torch.equal(out, ref), replay
+
+
+def test_a_call_takes_the_host_the_same_time_for_any_number_of_maps():
+    # 1,024 times as many maps, three launches either way
+    def host_us(n):
+        b = Batch([(2, 2, 2)] * n, 4)
+        occ = torch.zeros(b.total, dtype=torch.uint8, device="cuda")
+        out = torch.empty(b.total, dtype=torch.int32, device="cuda")
+        best = float("inf")
+        for _ in range(20):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            b.run(occ, out=out, mode=PHASED, tune={"lrun": 16, "schedule": 1})
+            best = min(best, (time.perf_counter() - t) * 1e6)
+        assert (out == 16).all()
+        return best
+    few, many = host_us(64), host_us(65536)
+    assert many < 4 * few, (few, many)
 
 
 def test_autotuner_picks_a_launch_mode_and_schedule(tmp_path, monkeypatch):
