@@ -729,6 +729,7 @@ struct edt_batch {
     MapDev* host_maps;       // in processing order
     int last_lrun[TABLES];   // run length that each set of item tables is for
     int lrun[TABLES][65];    // run length taken for a caller's, per set
+    int64_t items[65];       // most items of a phase, per run length
     int cus;
 };
 
@@ -741,9 +742,18 @@ namespace {
 // one map's items (the mean map's here).  Told once, when the batch is made: a
 // walk over 65,536 maps takes the host 79 us.
 void run_lengths(edt_batch* b) {
-    int64_t runs[65] = {};
-    for (int i = 0; i < b->n; ++i)
-        for (int l = 1; l <= 64; ++l) runs[l] += phase_items(b->host_maps[i], 1, l);
+    int64_t runs[65] = {}, zruns[65] = {}, words = 0;
+    for (int i = 0; i < b->n; ++i) {
+        words += phase_items(b->host_maps[i], 0, 1);
+        for (int l = 1; l <= 64; ++l) {
+            runs[l] += phase_items(b->host_maps[i], 1, l);
+            zruns[l] += phase_items(b->host_maps[i], 2, l);
+        }
+    }
+    for (int l = 1; l <= 64; ++l) {
+        const int64_t most = runs[l] > zruns[l] ? runs[l] : zruns[l];
+        b->items[l] = most > words ? most : words;
+    }
     for (int t = 0; t < TABLES; ++t)
         for (int l = 1; l <= 64; ++l) {
             int e = l;
@@ -751,6 +761,12 @@ void run_lengths(edt_batch* b) {
             b->lrun[t][l] = e;
         }
 }
+
+// Waves per CU of the fused launch at most, and no more of them than items: a
+// workgroup costs it two grid barriers.  24 maps of 32 to 256 voxels a side at
+// d_max 24, one obstacle in 50 voxels, 32 waves asked for: 20 a CU (what the
+// registers allow) 600 us, 16 545, 12 513, 8 527; two maps of 32 a side 280 -> 38.
+constexpr int FUSED_WAVES = 12;
 
 template <bool F16>
 edt_status launch_batch(edt_batch* b, const BArgs& a, int mode, int waves_per_cu, int wg_waves,
@@ -764,11 +780,14 @@ edt_status launch_batch(edt_batch* b, const BArgs& a, int mode, int waves_per_cu
             return EDT_ERR_HIP;
         int wgs_per_cu =
             waves_per_cu > 0 ? (waves_per_cu + wg_waves - 1) / wg_waves : 8 / wg_waves;
+        if (wgs_per_cu > FUSED_WAVES / wg_waves) wgs_per_cu = FUSED_WAVES / wg_waves;
         if (wgs_per_cu < 1) wgs_per_cu = 1;
-        const int g = b->cus * (wgs_per_cu < per_cu ? wgs_per_cu : per_cu);
+        int64_t g = (int64_t)b->cus * (wgs_per_cu < per_cu ? wgs_per_cu : per_cu);
+        const int64_t need = (b->items[a.lrun] + wg_waves - 1) / wg_waves;
+        if (g > need) g = need;
         if (g < 1) return EDT_ERR_HIP;
         void* args[] = {(void*)&a};
-        if (hipLaunchCooperativeKernel((const void*)k_batch_fused<F16>, dim3(g), dim3(bs), args,
+        if (hipLaunchCooperativeKernel((const void*)k_batch_fused<F16>, dim3((unsigned)g), dim3(bs), args,
                                        (unsigned)lds, st) != hipSuccess)
             return EDT_ERR_HIP;
         return EDT_OK;
