@@ -153,7 +153,8 @@ void launch_win(const Grid& g, int grid, hipStream_t st, const int32_t* items, i
     }
 }
 
-// Most blocks of a work item along an axis.
+// Most blocks of a work item along an axis: with d_max <= 255, R is 32 at most.
+constexpr int HULL_BLOCKS = LRUN + 2 * 32;
 inline int hull_item_blocks(const Grid& g, int axis) {
     const int most = g.lrun + 2 * g.R, extent = axis == 1 ? g.nby : g.nbz;
     return most < extent ? most : extent;
@@ -396,10 +397,9 @@ edt_status edt_create(const edt_config* cfg, void* d_ws, int64_t ws_bytes, void*
             free(c);
             return EDT_ERR_ARG;
         }
-        if (hipFuncSetAttribute((const void*)k_pass_hull<1>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, ly) != hipSuccess ||
-            hipFuncSetAttribute((const void*)k_pass_hull<2>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, lz) != hipSuccess) {
+        const int my = hull_item_lds<uint16_t>(HULL_BLOCKS), mz = hull_item_lds<uint32_t>(HULL_BLOCKS);
+        if (!hull_allow_lds((const void*)k_pass_hull<1>, my < lds_max ? my : lds_max) ||
+            !hull_allow_lds((const void*)k_pass_hull<2>, mz < lds_max ? mz : lds_max)) {
             free(c);
             return EDT_ERR_HIP;
         }

@@ -864,6 +864,15 @@ void with_row_lanes(int nw, F&& f) {
 }
 // LDS of the row records of a group along y.
 int row_lds_bytes(int ny) { return edt::hull_bands(ny) * edt::HB * (int)sizeof(uint2); }
+// LDS of a group in the two hull passes.
+int hull_lds_y(int ny) { return edt::hull_lds_bytes<uint16_t>(ny) + row_lds_bytes(ny); }
+int hull_lds_z(int nz) { return edt::hull_lds_bytes<uint32_t>(nz); }
+template <bool INC>
+bool hull_lds_allowed() {
+    using namespace edt;
+    return hull_allow_lds((const void*)k_dense_hull<1, INC>, hull_lds_y(HULL_N)) &&
+           hull_allow_lds((const void*)k_dense_hull<2, INC>, hull_lds_z(HULL_N));
+}
 dim3 hull_threads(int n) { return dim3((edt::hull_bands(n) * edt::HC + 63) & ~63); }
 
 // The three passes of the dense transform on `st`: x into g1, y from g1 into
@@ -876,6 +885,7 @@ edt_status launch_dense3(int32_t nx, int32_t ny, int32_t nz, int32_t d_max, cons
     const int32_t cap = d_max > 0 ? d_max * d_max : DINF;
     const DenseMarks none{};
     if (hull_ok(nx, ny, nz)) {
+        if (!hull_lds_allowed<false>()) return EDT_ERR_HIP;
         const int nw = row_words(nx);
         uint2* rec = (uint2*)g1;
         with_row_lanes(nw, [&](auto lanes) {
@@ -885,10 +895,10 @@ edt_status launch_dense3(int32_t nx, int32_t ny, int32_t nz, int32_t d_max, cons
                                0, st, nx, ny, nz, nw, d_occ, rec);
         });
         hipLaunchKernelGGL((k_dense_hull<1, false>), dim3(grid_of((int64_t)nw * nz, 65536)),
-                           hull_threads(ny), hull_lds_bytes<uint16_t>(ny) + row_lds_bytes(ny), st, nx, ny, nz, nw,
+                           hull_threads(ny), hull_lds_y(ny), st, nx, ny, nz, nw,
                            (const uint2*)rec, (const int32_t*)nullptr, g2, (int32_t)DINF, none);
         hipLaunchKernelGGL((k_dense_hull<2, false>), dim3(grid_of((int64_t)nw * ny, 65536)),
-                           hull_threads(nz), hull_lds_bytes<uint32_t>(nz), st, nx, ny, nz, nw,
+                           hull_threads(nz), hull_lds_z(nz), st, nx, ny, nz, nw,
                            (const uint2*)nullptr, (const int32_t*)g2, s, cap, none);
         return hipGetLastError() == hipSuccess ? EDT_OK : EDT_ERR_HIP;
     }
@@ -1066,10 +1076,12 @@ edt_status edt_dense_ctx_update(edt_dense_ctx* c, const int32_t* d_xyz, const ui
     if (n == 0) return EDT_OK;
     if (!d_xyz || !d_state) return EDT_ERR_ARG;
     if (n > c->max_changes) return EDT_ERR_CAPACITY;
+    const int nx = c->nx, ny = c->ny, nz = c->nz, nxc = (nx + 63) / 64;
+    const bool hulls = hull_ok(nx, ny, nz);
+    if (hulls && !hull_lds_allowed<true>()) return EDT_ERR_HIP;
     hipStream_t st = (hipStream_t)stream;
     const DenseLayout& L = c->L;
     char* b = c->ws;
-    const int nx = c->nx, ny = c->ny, nz = c->nz, nxc = (nx + 63) / 64;
     unsigned long long* ukeys = (unsigned long long*)(b + L.ukeys);
     int32_t* uvals = (int32_t*)(b + L.uvals);
     int32_t* upos = (int32_t*)(b + L.upos);
@@ -1085,7 +1097,7 @@ edt_status edt_dense_ctx_update(edt_dense_ctx* c, const int32_t* d_xyz, const ui
                        ukeys, uvals, (const int32_t*)upos, c->mk);
     // listed rows (at most n), then the listed y and z groups
     const int32_t cap = c->d_max > 0 ? c->d_max * c->d_max : DINF;
-    if (hull_ok(nx, ny, nz)) {
+    if (hulls) {
         const int nw = row_words(nx);
         uint2* rec = (uint2*)g1;
         with_row_lanes(nw, [&](auto lanes) {
@@ -1094,10 +1106,10 @@ edt_status edt_dense_ctx_update(edt_dense_ctx* c, const int32_t* d_xyz, const ui
                                dim3(256), 0, st, nx, ny, nw, (const uint8_t*)occ, rec, c->mk);
         });
         hipLaunchKernelGGL((k_dense_hull<1, true>), dim3(grid_of((int64_t)nw * nz, 2048)),
-                           hull_threads(ny), hull_lds_bytes<uint16_t>(ny) + row_lds_bytes(ny), st, nx, ny, nz, nw,
+                           hull_threads(ny), hull_lds_y(ny), st, nx, ny, nz, nw,
                            (const uint2*)rec, (const int32_t*)nullptr, g2, (int32_t)DINF, c->mk);
         hipLaunchKernelGGL((k_dense_hull<2, true>), dim3(grid_of((int64_t)nw * ny, 8192)),
-                           hull_threads(nz), hull_lds_bytes<uint32_t>(nz), st, nx, ny, nz, nw,
+                           hull_threads(nz), hull_lds_z(nz), st, nx, ny, nz, nw,
                            (const uint2*)nullptr, (const int32_t*)g2, sf, cap, c->mk);
         return hipGetLastError() == hipSuccess ? EDT_OK : EDT_ERR_HIP;
     }

@@ -63,6 +63,14 @@ __host__ __device__ inline HullLds<T> hull_lds(unsigned char* p, int n) {
     return h;
 }
 
+// Lets a kernel take `bytes` of LDS for its envelopes.  The limit belongs to the
+// kernel and the whole process: every caller sets the most the kernel can ever
+// ask for, so that none lowers it for another.
+inline bool hull_allow_lds(const void* kernel, int bytes) {
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) ==
+           hipSuccess;
+}
+
 // Product of two signed 24-bit values (one full-rate instruction; the
 // compiler falls back to the quarter-rate 32-bit product where it cannot
 // prove the ranges).

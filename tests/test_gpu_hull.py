@@ -109,3 +109,39 @@ def test_sparse_field_beyond_radius_64(shape, d_max):
         f.update(cu(xyz), cu(st))
         assert np.array_equal(f.dense().cpu().numpy(), oracle.edt_separable(occ, d_max)), step
     assert f.error() == 0
+
+
+def test_a_small_field_made_after_a_large_one():
+    # the passes of both are the same kernels with very different needs of LDS
+    rng = np.random.default_rng(6)
+    shapes = [(1040, 9, 11), (9, 1040, 11), (16, 16, 16)]
+    maps = [(rng.random(s) < 4.0 / np.prod(s)).astype(np.uint8) for s in shapes]
+    fields = [Field(s[::-1], 255 if max(s) > 16 else 65, max_changes=16) for s in shapes]
+    for f, occ in reversed(list(zip(fields, maps))):
+        occ.reshape(-1)[0] = 1
+        f.global_(cu(occ))
+        occ[tuple(n // 2 for n in occ.shape)] = 1
+        f.update(cu(np.array([[n // 2 for n in occ.shape[::-1]]], np.int32)), cu(np.ones(1, np.uint8)))
+        assert np.array_equal(f.dense().cpu().numpy(), oracle.edt_separable(occ, f.d_max)), occ.shape
+        assert f.error() == 0
+
+
+def test_captured_transform_of_the_longest_columns():
+    shape = (1024, 1024, 3)
+    occ, small = draw(shape, "scattered"), draw((8, 8, 8), "scattered")
+    src = cu(occ)
+    out = torch.empty(shape, dtype=torch.int32, device="cuda")
+    ws = torch.empty(8 * occ.size, dtype=torch.uint8, device="cuda")
+    dense_global(src, 0, out=out, workspace=ws)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        dense_global(src, 0, out=out, workspace=ws)
+    for seed in range(3):
+        occ = np.roll(occ, 5, axis=1)
+        src.copy_(cu(occ))
+        assert np.array_equal(dense_global(cu(small)).cpu().numpy(), ref(small, 0))
+        out.fill_(-7)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy(), ref(occ, 0)), seed
