@@ -155,7 +155,10 @@ __device__ inline void item_x(const BArgs& a, const MapDev& m, int li) {
     }
     __builtin_amdgcn_wave_barrier();
     const int bit = (int)(at - at0) + head;
-    const uint32_t* b32 = (const uint32_t*)bits + (bit >> 5);
+    // (two words of the pieces: copied, since a 32-bit read of 16-bit objects is
+    // the compiler's to move in front of their stores)
+    uint32_t b32[2];
+    __builtin_memcpy(b32, __builtin_assume_aligned(slice + 4 * (bit >> 5), 4), 8);
     const int here = min(32, m.nx - 32 * w);                  // voxels of the word in the row
     uint32_t word = __builtin_amdgcn_alignbit(b32[1], b32[0], bit & 31) &
                     (here == 32 ? ~0u : (1u << here) - 1u);
