@@ -35,7 +35,6 @@ namespace edt {
 
 constexpr unsigned long long KEY_EMPTY = ~0ull;
 constexpr int LRUN = 64;        // longest y / z work item (blocks); Grid::lrun <= LRUN
-constexpr int32_t FINF = 1 << 28;
 
 enum : uint32_t {
     F_DILATED = 1u,  // block's R-neighbourhood is in the pool

@@ -1250,7 +1250,7 @@ __global__ void __launch_bounds__(64) k_pass_win(Grid g, const int32_t* items, i
             const int32_t slot1 = __builtin_amdgcn_readfirstlane(has1 ? sl[base + ob + 1] : -1);
             win_store<AXIS, F16>(g, slot0, slot1, acc, lane);
         };
-        window_min<M, false, F16>(hb, len, Dp, blk, emit, [](int) { return true; }, sk);
+        window_min<M, F16>(hb, len, Dp, blk, emit, [](int) { return true; }, sk);
         finish_run(g, sl, len, AXIS, runflag);
         __syncthreads();
     }
@@ -1351,7 +1351,7 @@ __global__ void __launch_bounds__(64) k_pass_win_tiles(Grid g) {
                 win_store<AXIS, F16>(g, slot0, slot1, acc, lane);
             };
             auto need = [&](int ob) { return sl[M + ob] >= 0 || sl[M + ob + 1] >= 0; };
-            window_min<M, false, F16>(j0, SPLIT ? count : 8, Dpw, blk, emit, need, sk);
+            window_min<M, F16>(j0, SPLIT ? count : 8, Dpw, blk, emit, need, sk);
         }
         __syncthreads();
     }

@@ -111,14 +111,9 @@ struct WinSkip {
 
 // need(ob): false when neither output block ob nor ob + 1 is wanted (must be
 // uniform across the wave); the window still slides over such a pair.
-// LB: before each offset group G >= 1, also test a per-lane bound (the least
-// input in the group's position ranges plus (8G)^2 against the lane's largest
-// output) and skip the group when no lane can improve.  It pays on maps where
-// most groups are decided that way (dense maps), not where the block bounds
-// already skip them.
 // F16: values are binary16 bit patterns (see above); Dp then holds D as two
 // binary16 halves, and so do the outputs handed to emit.
-template <int M, bool LB = false, bool F16 = false, class Blk, class Emit, class Need>
+template <int M, bool F16 = false, class Blk, class Emit, class Need>
 __device__ inline void window_min(int first, int count, uint32_t Dp, Blk&& blk, Emit&& emit,
                                   Need&& need, const WinSkip& sk) {
     constexpr int NW = 2 * M + 2;        // window blocks
@@ -167,35 +162,10 @@ __device__ inline void window_min(int first, int count, uint32_t Dp, Blk&& blk, 
                 // k >= 1) reads blocks ob - G - 1 .. ob - G + 1 and
                 // ob + G .. ob + G + 2; the two candidates at +-k share k^2,
                 // so min(in(i - k), in(i + k)) + k^2 covers both
-                // per-lane bound: group G offers candidates no smaller than the
-                // least input in its two position ranges plus (8G)^2; mx is the
-                // lane's largest output so far (both halves)
-                u16x2 mx = LB ? max8<F16>(acc) : acc[0];
 #pragma unroll
                 for (int G = 0; G < M; ++G) {
                     const uint64_t CG = (7ull << (M - G - 1)) | (7ull << (M + G));
                     if (((sk.g[G] >> sh) & CG) == CG) continue;
-                    if (LB && G > 0) {
-                        // candidates of group G for output o lie at o + 8M -+ k,
-                        // k = 8G .. 8G + 7: positions 8M - 8G - 7 .. 8M - 8G + 7
-                        // and 8M + 8G .. 8M + 8G + 14 (packed: the high half
-                        // covers the outputs o + 8)
-                        u16x2 lb = P[8 * M - 8 * G - 7];
-#pragma unroll
-                        for (int q = 8 * M - 8 * G - 6; q <= 8 * M - 8 * G + 7; ++q)
-                            lb = __builtin_elementwise_min(lb, P[q]);
-#pragma unroll
-                        for (int q = 8 * M + 8 * G; q <= 8 * M + 8 * G + 14 && q < NP; ++q)
-                            lb = __builtin_elementwise_min(lb, P[q]);
-                        if (F16) {
-                            const _Float16 g2 = (_Float16)(64 * G * G);
-                            lb = as_u16x2(as_h16x2(lb) + (h16x2){g2, g2});
-                        } else {
-                            const unsigned short g2 = (unsigned short)(64 * G * G);
-                            lb = lb + (u16x2){g2, g2};
-                        }
-                        if (!__any(lb.x < mx.x || lb.y < mx.y)) continue;
-                    }
                     const int k0 = G == 0 ? 1 : 8 * G, k1 = 8 * G + 7;
                     // one side of the group can be skipped on its own: the
                     // candidates of offsets -k then come from the blocks
@@ -248,7 +218,7 @@ __device__ inline void window_min(int first, int count, uint32_t Dp, Blk&& blk, 
                     // are <= (8G + 8)^2, the least any further candidate adds
                     // (binary16 patterns order like their values)
                     if (G + 1 < M) {
-                        mx = max8<F16>(acc);
+                        const u16x2 mx = max8<F16>(acc);
                         const uint32_t sq = (8 * G + 8) * (8 * G + 8);
                         const int lim = F16 ? (int)f16_bits(sq) : (int)sq;
                         const bool more = (int)mx.x > lim || (int)mx.y > lim;
@@ -274,11 +244,6 @@ __device__ inline void window_min(int first, int count, uint32_t Dp, Blk&& blk, 
         Wl = N1;
         if (need(ob)) emit(ob, acc, ob + 1 < first + count);
     }
-}
-
-template <int M, bool LB = false, bool F16 = false, class Blk, class Emit>
-__device__ inline void window_min(int first, int count, uint32_t Dp, Blk&& blk, Emit&& emit) {
-    window_min<M, LB, F16>(first, count, Dp, blk, emit, [](int) { return true; }, WinSkip{});
 }
 
 }  // namespace edt
