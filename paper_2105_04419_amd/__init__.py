@@ -484,7 +484,7 @@ class DenseField:
 def dense_global_noalloc(occ: torch.Tensor, d_max: int = 0, out: torch.Tensor | None = None,
                          stream=None) -> torch.Tensor:
     """dense_global without a workspace (edt_dense_global_noalloc): the
-    library's static per-GPU buffer holds the envelopes, so grids are limited
+    library's static per-GPU buffer takes the workspace's place, so grids are limited
     to DENSE_STATIC_BYTES / 8 voxels.  Calls that overlap on one GPU race.
     With `out` given, the call itself allocates nothing."""
     nz, ny, nx = (int(v) for v in occ.shape)
@@ -519,9 +519,9 @@ def _clearance_args(s, wp):
 
 # The calls themselves, on arguments that _clearance_args has passed and an
 # output of the right type and shape.  A cost and its gradient are 12 us of
-# kernels, so the time of the pair is this host path: checked once, it went
-# from 118 to 79 us (4096 trajectories of 64 waypoints) with the stream's
-# handle taken directly.
+# kernels, so the time of the pair is this host path: checked once and with
+# the stream's handle taken directly, it went from 118 to 79 us (4096
+# trajectories of 64 waypoints) on one host and from 73 to 61 on another.
 def _clearance_fwd(s, wp, h, margin, out, stream=None):
     nz, ny, nx = s.shape
     T, W, _ = wp.shape

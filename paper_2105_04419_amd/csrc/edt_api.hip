@@ -541,7 +541,7 @@ edt_status edt_grow(edt_ctx* c, int64_t max_blocks, void* d_ws, int64_t ws_bytes
     if (ws_bytes < L.total) return EDT_ERR_CAPACITY;
     hipStream_t st = S(stream);
     const Grid o = c->g;
-    edt_ctx n = *c;              // timing events, call number, envelope sizes carry over
+    edt_ctx n = *c;              // timing events and the call number carry over
     bind_workspace(&n, &cfg, L, (char*)d_ws);
     edt_status e = init_workspace(&n, L, st);
     if (e != EDT_OK) return e;

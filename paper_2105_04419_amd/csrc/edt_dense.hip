@@ -25,15 +25,16 @@
 //       compared exactly as int64 cross products, then read off left to
 //       right.  The envelope of every column lives in the workspace (one int2
 //       (v, f) per voxel), entry k of column c at k * ncols + c.
-// On the 1024 x 1024 x 128 tunnel extent the first form takes 0.85 ms, the
-// second 2.99 ms (its stacks are touched one cache line per lane and push).
+// On the 1024 x 1024 x 128 tunnel extent the first form takes 0.81 ms, the
+// second 2.9 ms (its stacks are touched one cache line per lane and push).
 //
 // The dense context (edt_dense_ctx_*) keeps the occupancy and both
-// intermediates (g1 after x, g2 after y) beside the field, so a change list
-// is applied incrementally and exactly: the rows holding a changed voxel are
-// recomputed by pass x; a y column is recomputed when some g1 value in it
-// changed, a z column when some g2 value in it changed.  Columns are handled
-// in groups of 64 consecutive x (one wave), marked by the pass before
+// intermediates (g1 after x: records or distances; g2 after y) beside the
+// field, so a change list is applied incrementally and exactly: the rows
+// holding a changed voxel are recomputed by pass x; a y column is recomputed
+// when some g1 value in it changed, a z column when some g2 value in it
+// changed.  Columns are handled in groups of 32 consecutive x (64 with sides
+// too long for the hulls), marked by the pass before
 // (a flag per group and a list of the marked groups), so every recomputed
 // column is an exact pass over its whole length and the field equals the
 // global transform of the new occupancy.
@@ -89,8 +90,8 @@ __device__ inline uint32_t chunk_bits(const uint8_t* row, int x0, int nx, int la
 // Marks of an incremental update (dense context).  cnt: [0] error word,
 // [1] the current call is cancelled (set by the dedupe, read by the apply
 // kernel, cleared by the pass-x kernel), [2] rows listed, [3] y groups listed,
-// [4] z groups listed.  A y group is (x / 64, z), a z group (x / 64, y); one
-// wave recomputes the group's 64 columns.
+// [4] z groups listed.  A y group is (x / n, z), a z group (x / n, y), with n =
+// 32 columns recomputed by one workgroup (hulls) or 64 by one wave.
 struct DenseMarks {
     int32_t* cnt;
     int32_t* rowflag;        // [ny * nz] row listed for pass x

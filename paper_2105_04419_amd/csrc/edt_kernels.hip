@@ -661,7 +661,7 @@ __device__ inline void x_strip(const Grid& g, const int32_t* sl, const uint32_t 
     // least g1 of each block: 0 on a row holding an obstacle, else set
     // by the end voxels (voxel 0 is nearest the left obstacle, voxel 7
     // the right one).  lc: distance from the voxel before block j to
-    // the nearest obstacle at or before it.  The squares (<= 64^2) are
+    // the nearest obstacle at or before it.  The squares (<= 255^2) are
     // reduced over the wave two blocks at a time, packed.
     uint32_t bmins[4];
     {

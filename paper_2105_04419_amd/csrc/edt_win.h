@@ -117,7 +117,6 @@ template <int M, bool F16 = false, class Blk, class Emit, class Need>
 __device__ inline void window_min(int first, int count, uint32_t Dp, Blk&& blk, Emit&& emit,
                                   Need&& need, const WinSkip& sk) {
     constexpr int NW = 2 * M + 2;        // window blocks
-    constexpr int K = 8 * M - 1;         // largest offset
     constexpr int NP = 8 * (NW - 1);     // input pairs: positions p = -8M .. 8M + 7
     // P[q]: (in(p), in(p + 8)) for p = q - 8M relative to the step's first
     // output, packed.  The window slides by 16 positions per step, so all but
