@@ -868,11 +868,14 @@ int row_lds_bytes(int ny) { return edt::hull_bands(ny) * edt::HB * (int)sizeof(u
 // LDS of a group in the two hull passes.
 int hull_lds_y(int ny) { return edt::hull_lds_bytes<uint16_t>(ny) + row_lds_bytes(ny); }
 int hull_lds_z(int nz) { return edt::hull_lds_bytes<uint32_t>(nz); }
+// (64 KB need no leave)
 template <bool INC>
-bool hull_lds_allowed() {
+bool hull_lds_allowed(int ny, int nz) {
     using namespace edt;
-    return hull_allow_lds((const void*)k_dense_hull<1, INC>, hull_lds_y(HULL_N)) &&
-           hull_allow_lds((const void*)k_dense_hull<2, INC>, hull_lds_z(HULL_N));
+    return (hull_lds_y(ny) <= 65536 ||
+            hull_allow_lds((const void*)k_dense_hull<1, INC>, hull_lds_y(HULL_N))) &&
+           (hull_lds_z(nz) <= 65536 ||
+            hull_allow_lds((const void*)k_dense_hull<2, INC>, hull_lds_z(HULL_N)));
 }
 dim3 hull_threads(int n) { return dim3((edt::hull_bands(n) * edt::HC + 63) & ~63); }
 
@@ -886,7 +889,7 @@ edt_status launch_dense3(int32_t nx, int32_t ny, int32_t nz, int32_t d_max, cons
     const int32_t cap = d_max > 0 ? d_max * d_max : DINF;
     const DenseMarks none{};
     if (hull_ok(nx, ny, nz)) {
-        if (!hull_lds_allowed<false>()) return EDT_ERR_HIP;
+        if (!hull_lds_allowed<false>(ny, nz)) return EDT_ERR_HIP;
         const int nw = row_words(nx);
         uint2* rec = (uint2*)g1;
         with_row_lanes(nw, [&](auto lanes) {
@@ -1079,7 +1082,7 @@ edt_status edt_dense_ctx_update(edt_dense_ctx* c, const int32_t* d_xyz, const ui
     if (n > c->max_changes) return EDT_ERR_CAPACITY;
     const int nx = c->nx, ny = c->ny, nz = c->nz, nxc = (nx + 63) / 64;
     const bool hulls = hull_ok(nx, ny, nz);
-    if (hulls && !hull_lds_allowed<true>()) return EDT_ERR_HIP;
+    if (hulls && !hull_lds_allowed<true>(ny, nz)) return EDT_ERR_HIP;
     hipStream_t st = (hipStream_t)stream;
     const DenseLayout& L = c->L;
     char* b = c->ws;
