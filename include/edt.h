@@ -287,7 +287,8 @@ typedef struct {
  *                 without a wave (in PER_MAP a launch holds one map's items,
  *                 so its runs may be shorter than the other modes')
  *   waves_per_cu  most waves resident per compute unit (0 = default, <= 64;
- *                 the fused launch takes no more than 12)
+ *                 the fused launch takes no more than 12,
+ *                 rounded up to whole workgroups)
  *   chunk         work items taken per queue atomic (1 .. 1024)
  *   schedule      0 = dynamic queue, 1 = static stride
  *   wg_waves      waves per workgroup: 1, 2, 4 or 8 (0 = 4); each wave

@@ -765,10 +765,12 @@ void run_lengths(edt_batch* b) {
         }
 }
 
-// Waves per CU of the fused launch at most, and no more of them than items: a
-// workgroup costs it two grid barriers.  24 maps of 32 to 256 voxels a side at
-// d_max 24, one obstacle in 50 voxels, 32 waves asked for: 20 a CU (what the
-// registers allow) 600 us, 16 545, 12 513, 8 527; two maps of 32 a side 280 -> 38.
+// Waves per CU of the fused launch at most, in whole workgroups, and no more of
+// them than items: a workgroup costs it two grid barriers.  24 maps of 32 to 256
+// voxels a side at d_max 24, one obstacle in 50 voxels, 32 waves asked for in
+// workgroups of 4: 20 a CU (what the registers allow) 600 us, 16 545, 12 513, 8
+// 527; two maps of 32 a side 280 -> 38.  Workgroups of 8: two a CU are best (64
+// maps 663 us; with one 784).
 constexpr int FUSED_WAVES = 12;
 
 template <bool F16>
@@ -783,7 +785,8 @@ edt_status launch_batch(edt_batch* b, const BArgs& a, int mode, int waves_per_cu
             return EDT_ERR_HIP;
         int wgs_per_cu =
             waves_per_cu > 0 ? (waves_per_cu + wg_waves - 1) / wg_waves : 8 / wg_waves;
-        if (wgs_per_cu > FUSED_WAVES / wg_waves) wgs_per_cu = FUSED_WAVES / wg_waves;
+        const int most = (FUSED_WAVES + wg_waves - 1) / wg_waves;
+        if (wgs_per_cu > most) wgs_per_cu = most;
         if (wgs_per_cu < 1) wgs_per_cu = 1;
         int64_t g = (int64_t)b->cus * (wgs_per_cu < per_cu ? wgs_per_cu : per_cu);
         const int64_t need = (b->items[a.lrun] + wg_waves - 1) / wg_waves;
